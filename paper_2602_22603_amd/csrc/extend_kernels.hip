@@ -52,12 +52,11 @@ constexpr float kNegInf = -__builtin_huge_valf();
 // to 256 registers each).
 constexpr int kExtWavesPerEu = 2;
 
+typedef __bf16 bf16x2_t __attribute__((__vector_size__(2 * sizeof(__bf16))));
 typedef __bf16 bf16x8_t __attribute__((__vector_size__(8 * sizeof(__bf16))));
 typedef float f32x4_t __attribute__((__vector_size__(4 * sizeof(float))));
 
 __device__ inline float exp2_fast(float x) { return __builtin_amdgcn_exp2f(x); }
-__device__ inline float bf_lo(uint32_t x) { return __uint_as_float(x << 16); }
-__device__ inline float bf_hi(uint32_t x) { return __uint_as_float(x & 0xffff0000u); }
 
 __device__ inline float max_xrow16(float x) {
   auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
@@ -83,6 +82,22 @@ typedef __bf16 bf16x2v_t __attribute__((ext_vector_type(2)));
 // v_cvt_pk_bf16_f32).
 __device__ inline uint32_t pack_bf16(float lo, float hi) {
   return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2_t){lo, hi}, bf16x2v_t));
+}
+
+// p less the low or the high half of a packed pair of bf16 values: the dot
+// product with (-1, 0) or (0, -1) plus p, one instruction in place of
+// unpacking the half and subtracting.  Exact either way: p's bf16 rounding
+// is within a factor of two of p.  The factors come from registers (as a
+// constant the compiler turns (-1, 0) into the inline constant -1.0, which
+// this instruction reads as (0, -1)).
+__device__ inline uint32_t minus_one(int half) {
+  uint32_t x = half ? 0xbf800000u : 0xbf80u;
+  asm("" : "+s"(x));
+  return x;
+}
+__device__ inline float residue(uint32_t pair, uint32_t minus_one_at, float p) {
+  return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, pair),
+                                         __builtin_bit_cast(bf16x2_t, minus_one_at), p, false);
 }
 
 template <int D> struct ExtLayout {
@@ -114,7 +129,7 @@ template <int D> struct ExtLayout {
 //      makes 32 consecutive chunks per half-wave.
 template <int D> __device__ inline int k_phys(int row, int c) {
   if constexpr (D == 128) return c ^ ((row & 3) + 4 * ((row >> 3) & 3));
-  else return c ^ (2 * ((row >> 3) & 3));
+  else return c ^ ((row & 2) + 4 * ((row >> 4) & 1));
 }
 // Element offset, in a V^T block buffer, of keys 8 j .. 8 j + 7 of row d.
 template <int D> __device__ inline int v_off(int d, int j) {
@@ -328,6 +343,7 @@ __device__ __attribute__((always_inline)) inline void ext_block(const uint16_t *
           if (key > lim[cg] || key < first[cg] || !((lm >> (4 * tt + i)) & 1)) st[tt][cg][i] = kNegInf;
         }
   }
+  const uint32_t m1l = minus_one(0), m1h = minus_one(1);
   float nm[2];
 #pragma unroll
   for (int cg = 0; cg < 2; ++cg) nm[cg] = m_run[cg] == kNegInf ? 0.f : -m_run[cg];
@@ -346,7 +362,7 @@ __device__ __attribute__((always_inline)) inline void ext_block(const uint16_t *
           const float p0 = exp2_fast(fmaf(st[tt][cg][2 * (e & 1)], c, nm[cg]));
           const float p1 = exp2_fast(fmaf(st[tt][cg][2 * (e & 1) + 1], c, nm[cg]));
           h[e] = pack_bf16(p0, p1);
-          l[e] = pack_bf16(p0 - bf_lo(h[e]), p1 - bf_hi(h[e]));
+          l[e] = pack_bf16(residue(h[e], m1l, p0), residue(h[e], m1h, p1));
           psum[cg] += p0 + p1;
         }
         phi[cg] = __builtin_bit_cast(bf16x8_t, make_uint4(h[0], h[1], h[2], h[3]));
