@@ -9,11 +9,10 @@ namespace sq {
 
 // ---- extend (causal attention of an appended chunk) ------------------------
 // The chunk is the last n of the sequence's L tokens; new token j attends to
-// logical keys 0 .. L - n + j.  A workgroup of kExtWaves waves takes 32
-// query rows per wave (kExtRows / G tokens x the G query heads of one KV
-// head) against the whole key range; one workgroup fits a CU.
-constexpr int kExtWaves = 8;
-constexpr int kExtRows = 32 * kExtWaves;
+// logical keys 0 .. L - n + j.  A workgroup of 8, 4 or 2 waves takes 32 query
+// rows per wave (rows / G tokens x the G query heads of one KV head) against
+// the whole key range or a split of it; the host chooses rows and splits by
+// predicted time.
 constexpr int kExtKeys = 64; // keys per LDS block (4 pages)
 
 struct ExtendArgs {
@@ -29,7 +28,7 @@ struct ExtendArgs {
   int32_t n;          // new tokens
   int32_t hq;
   int32_t hkv;
-  int32_t n_qblocks;  // ceil(n / (kExtRows / G))
+  int32_t n_qblocks;  // ceil(n / (rows / G))
   float scale_log2;
   // Split of the key range (chunks too short to fill the GPU): each (query
   // block, KV head) runs n_split workgroups over split_blocks key blocks
@@ -37,9 +36,9 @@ struct ExtendArgs {
   // n_split == 1: the workgroup writes out directly.
   int32_t n_split;
   int32_t split_blocks;
-  float *part_m;      // [slots][kExtRows] (log2 units), slot = (qb * Hkv + g) * n_split + s
-  float *part_l;      // [slots][kExtRows]
-  float *part_acc;    // [slots][kExtRows][D]
+  float *part_m;      // [slots][rows] (log2 units), slot = (qb * Hkv + g) * n_split + s
+  float *part_l;      // [slots][rows]
+  float *part_acc;    // [slots][rows][D]
   // Model variants: a window of `window` keys (0: none) ends at each
   // token's own index; sinks[h] (or null) joins each softmax as a term with
   // no value, scaled by sink_scale into the log2 units of the scores.
@@ -52,7 +51,7 @@ struct ExtendArgs {
   int32_t masked;
   int32_t kv8;        // 1: the pools hold E4M3 codes (K scale in scale_log2)
   float out_scale;    // the layer's V scale in an 8-bit store (1 otherwise)
-  int32_t pad;
+  int32_t rows;       // query rows per workgroup, 32 per wave: 256, 128 or 64
 };
 
 static_assert(sizeof(ExtendArgs) < 4096, "extend kernel arguments too large");

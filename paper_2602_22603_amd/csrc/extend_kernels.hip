@@ -11,11 +11,16 @@
 //   workgroup = 8 waves (one workgroup per CU, two waves per SIMD), 256
 //               query rows = (256 / G tokens) x (G query heads of one KV
 //               head); each wave owns 32 rows as two MFMA column groups of
-//               16.
+//               16.  Chunks whose rows would leave much of such a tile to
+//               padding run 4 or 2 waves per workgroup, two workgroups per
+//               CU (77 tokens x 4 heads over 60.5K keys: 127 us with three
+//               128-row tiles, 152 with two of 256).
 //   K/V       = blocks of 64 keys (4 pages), copied global -> LDS by the
 //               gfx950 direct-to-LDS buffer loads (16 bytes a lane) into
 //               three buffers: blocks b + 1 and b + 2 are in flight while
-//               block b is computed, and no registers hold staging data.  K
+//               block b is computed, and no registers hold staging data (two
+//               buffers, one block in flight, for the narrow tiles of 128
+//               channels, so that two workgroups fit the CU's LDS).  K
 //               rows have their 16-byte chunks XOR-swizzled and V^T keeps
 //               the pool's page layout, so that the MFMA operand reads below
 //               are free of bank conflicts.
@@ -46,7 +51,6 @@ namespace sq {
 namespace {
 
 constexpr int BK = kExtKeys;
-constexpr int kThreads = 64 * kExtWaves;
 constexpr float kNegInf = -__builtin_huge_valf();
 // Two waves per SIMD: the eight waves of the one workgroup a CU holds (up
 // to 256 registers each).
@@ -100,33 +104,39 @@ __device__ inline float residue(uint32_t pair, uint32_t minus_one_at, float p) {
                                          __builtin_bit_cast(bf16x2_t, minus_one_at), p, false);
 }
 
-template <int D> struct ExtLayout {
+template <int D, int W> struct ExtLayout {
   static constexpr int CH = D / 8;             // 16-byte chunks per K row
   static constexpr int KROWS = 1024 / (2 * D); // K rows one wave-wide DMA writes
   static constexpr int K_ELEMS = BK * D;       // bf16 per K buffer
   static constexpr int V_ELEMS = D * BK;       // bf16 per V^T buffer
-  static constexpr int NK = K_ELEMS * 2 / 1024 / kExtWaves; // K DMAs per wave per block
-  static constexpr int NV = V_ELEMS * 2 / 1024 / kExtWaves; // V DMAs per wave per block
-  static constexpr int PW = NK * KROWS;  // a wave's copies cover keys of page (wave * PW) / kPage
-  static_assert(NK * kExtWaves * KROWS == BK && kPage % PW == 0, "a wave's copies stay in one page");
-  static_assert(NV * 1024 == kPage * D * 2 * 4 / kExtWaves, "V^T copies split evenly");
+  static constexpr int NK = K_ELEMS * 2 / 1024 / W; // K DMAs per wave per block
+  static constexpr int NV = V_ELEMS * 2 / 1024 / W; // V DMAs per wave per block
+  static constexpr int KPP = kPage / KROWS; // K copy instructions that fill a page
+  static constexpr int VPP = kPage * D * 2 / 1024; // and V^T ones
+  static constexpr int NP = NK > KPP ? NK / KPP : 1; // pages a wave's copies cover
+  // block buffers: two for an 8-bit store (whose copies pass through
+  // registers) and where two or more workgroups are to share a CU's LDS
+  static constexpr int NB = D == 128 && W < 8 ? 2 : 3;
+  static_assert(KPP == VPP && (NK % KPP == 0 || KPP % NK == 0), "a wave copies whole pages or a part of one");
 };
 
-// LDS layouts.  A 16-byte LDS read (ds_read_b128) is served half a wave at
-// a time from 128 four-byte banks (measured on gfx950 with the
-// bank-conflict counter), so it is conflict-free when the 32 chunks a
-// half-wave reads are distinct modulo 32.
+// LDS layouts.  A 16-byte LDS read (ds_read_b128) is served 16 lanes at a
+// time from 64 four-byte banks, the 16 being lanes 0-3, 12-15, 20-23 and
+// 24-27, or 4-11, 16-19 and 28-31, of each half-wave (measured on gfx950 with
+// the bank-conflict counter), so it is conflict-free when the chunks of each
+// such set are distinct modulo 16.
 //   K: one row of D channels per key; an operand read has lane (n, kg) read
 //      logical chunk 4 kc + kg of row tile_key(t, n) = 32a + 8(n >> 2) + 4h
 //      + (n & 3), so chunks are XOR-swizzled within the row.  With 256-byte
-//      rows the key (n & 3) + 4 (n >> 2) = n spreads the 8 rows of each
-//      parity over all 16 slots; with 128-byte rows rows of equal n & 3
-//      share a bank quarter, and 2 (n >> 2) separates them.
+//      rows the key (n & 3) + 4 (n >> 2) = n gives kg ^ n, distinct in each
+//      set.  With 128-byte rows two rows share the banks, the row's parity
+//      choosing the half, and bit 1 of n & 3 and of n >> 2 separate the rest
+//      (within a set kg tells n >> 2 = 0, 3 from 1, 2).
 //   V^T: the block's four pages one after another, each as the pool holds
 //      it (D rows of 16 keys, 32 bytes), so a page is copied as it lies.  A
 //      P.V operand read has lane (n, kg) read keys 8 (4 c2 + kg) .. +7 of row
-//      d = 16 dt + n: page 2 c2 + kg / 2, chunk 2 d + kg % 2 of it, which
-//      makes 32 consecutive chunks per half-wave.
+//      d = 16 dt + n: page 2 c2 + kg / 2, chunk 2 d + kg % 2 of it, distinct
+//      in each set.
 template <int D> __device__ inline int k_phys(int row, int c) {
   if constexpr (D == 128) return c ^ ((row & 3) + 4 * ((row >> 3) & 3));
   else return c ^ ((row & 2) + 4 * ((row >> 4) & 1));
@@ -184,33 +194,36 @@ __device__ inline __amdgpu_buffer_rsrc_t ext_page(const void *page, int bytes) {
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(page), (short)0, bytes, 0x00020000);
 }
 
-// Global -> LDS (direct) for one block: each wave copies a part of one page
-// of the block, K rows and V^T alike, so one page address per wave serves
-// all of its copy instructions (formed by the scalar unit from the page id)
-// and the lanes add offsets that do not change from block to block.
-template <int D>
+// Global -> LDS (direct) for one block: each wave copies NP whole pages of the
+// block, or a part of one, K rows and V^T alike, so one page address (formed by
+// the scalar unit from the page id) serves all copy instructions of a page and
+// the lanes add offsets that do not change from block to block.
+template <int D, int W>
 __device__ inline void ext_dma(uint16_t *sk, uint16_t *sv, const ExtendArgs &a,
                                const uint16_t *kbase, const uint16_t *vbase,
                                const int32_t (&ids)[4], int wave, int lane) {
-  using Lt = ExtLayout<D>;
+  using Lt = ExtLayout<D, W>;
   constexpr int kPageBytes = kPage * D * 2;
-  constexpr int IPP = kPageBytes / 1024; // copy instructions per page
-  const int64_t off = (int64_t)pick4(ids, wave * Lt::PW / kPage) * a.page_stride;
-  const __amdgpu_buffer_rsrc_t kr = ext_page(kbase + off, kPageBytes);
-  const __amdgpu_buffer_rsrc_t vr = ext_page(vbase + off, kPageBytes);
+  constexpr int IPP = Lt::KPP, PER = Lt::NK / Lt::NP; // instructions per page; this wave's of each
 #pragma unroll
-  for (int u = 0; u < Lt::NK; ++u) {
-    const int ins = wave * Lt::NK + u;
-    const int row = ins * Lt::KROWS + lane / Lt::CH;
-    const int c = k_phys<D>(row, lane % Lt::CH); // the swizzle is an involution
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(kr, (lds_void *)(sk + ins * 512), 16,
-                                             ((row % kPage) * D + 8 * c) * 2, 0, 0, 0);
-  }
+  for (int pg = 0; pg < Lt::NP; ++pg) {
+    const int64_t off = (int64_t)pick4(ids, (wave * Lt::NK + pg * PER) / IPP) * a.page_stride;
+    const __amdgpu_buffer_rsrc_t kr = ext_page(kbase + off, kPageBytes);
+    const __amdgpu_buffer_rsrc_t vr = ext_page(vbase + off, kPageBytes);
 #pragma unroll
-  for (int u = 0; u < Lt::NV; ++u) {
-    const int ins = wave * Lt::NV + u;
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(vr, (lds_void *)(sv + ins * 512), 16,
-                                             ((ins % IPP) * 512 + lane * 8) * 2, 0, 0, 0);
+    for (int u = pg * PER; u < (pg + 1) * PER; ++u) {
+      const int ins = wave * Lt::NK + u;
+      const int row = ins * Lt::KROWS + lane / Lt::CH;
+      const int c = k_phys<D>(row, lane % Lt::CH); // the swizzle is an involution
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(kr, (lds_void *)(sk + ins * 512), 16,
+                                               ((row % kPage) * D + 8 * c) * 2, 0, 0, 0);
+    }
+#pragma unroll
+    for (int u = pg * PER; u < (pg + 1) * PER; ++u) {
+      const int ins = wave * Lt::NV + u;
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(vr, (lds_void *)(sv + ins * 512), 16,
+                                               ((ins % IPP) * 512 + lane * 8) * 2, 0, 0, 0);
+    }
   }
 }
 
@@ -218,17 +231,17 @@ __device__ inline void ext_dma(uint16_t *sk, uint16_t *sv, const ExtendArgs &a,
 // codes each lane's DMA would have copied as 8 bf16 values (half the bytes);
 // ext_store8 converts them and writes the bf16 tile exactly where the DMA
 // writes it, so the compute is unchanged.
-template <int D>
-__device__ inline void ext_load8(uint2 (&kr)[ExtLayout<D>::NK], uint2 (&vr)[ExtLayout<D>::NV],
+template <int D, int W, int N>
+__device__ inline void ext_load8(uint2 (&kr)[N], uint2 (&vr)[N],
                                  const ExtendArgs &a, const uint8_t *kbase, const uint8_t *vbase,
                                  const int32_t (&ids)[4], int wave, int lane) {
-  using Lt = ExtLayout<D>;
+  using Lt = ExtLayout<D, W>;
 #pragma unroll
   for (int u = 0; u < Lt::NK; ++u) {
     const int ins = wave * Lt::NK + u;
     const int row = ins * Lt::KROWS + lane / Lt::CH;
     const int c = k_phys<D>(row, lane % Lt::CH);
-    const int p = (ins * Lt::KROWS) / kPage;
+    const int p = ins / Lt::KPP;
     kr[u] = *reinterpret_cast<const uint2 *>(kbase + (int64_t)pick4(ids, p) * a.page_stride +
                                              (row % kPage) * D + 8 * c);
   }
@@ -240,10 +253,10 @@ __device__ inline void ext_load8(uint2 (&kr)[ExtLayout<D>::NK], uint2 (&vr)[ExtL
                                              (ins % IPP) * 512 + lane * 8);
   }
 }
-template <int D>
-__device__ inline void ext_store8(uint16_t *sk, uint16_t *sv, const uint2 (&kr)[ExtLayout<D>::NK],
-                                  const uint2 (&vr)[ExtLayout<D>::NV], int wave, int lane) {
-  using Lt = ExtLayout<D>;
+template <int D, int W, int N>
+__device__ inline void ext_store8(uint16_t *sk, uint16_t *sv, const uint2 (&kr)[N],
+                                  const uint2 (&vr)[N], int wave, int lane) {
+  using Lt = ExtLayout<D, W>;
 #pragma unroll
   for (int u = 0; u < Lt::NK; ++u) {
     const uint2 lo = e4m3x4_to_bf16(kr[u].x), hi = e4m3x4_to_bf16(kr[u].y);
@@ -258,9 +271,9 @@ __device__ inline void ext_store8(uint16_t *sk, uint16_t *sv, const uint2 (&kr)[
 
 // Zero V^T entries of keys at or past L in the block's buffer (the last
 // block only), so that 0 * v stays 0 whatever the pool holds there.
-template <int D>
+template <int D, int W>
 __device__ inline void ext_zero_tail(uint16_t *sv, int blk, int L, int tid) {
-  for (int q = tid; q < D * 8; q += kThreads) {
+  for (int q = tid; q < D * 8; q += 64 * W) {
     const int d = q >> 3, j = q & 7;
     const int k0 = blk * BK + 8 * j;
     if (k0 + 8 <= L) continue;
@@ -417,20 +430,23 @@ __device__ __attribute__((always_inline)) inline void ext_block(const uint16_t *
   }
 }
 
-template <int D, int G, bool KV8 = false>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kExtWavesPerEu, kExtWavesPerEu))) void
+template <int D, int G, int W, bool KV8 = false>
+__global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(kExtWavesPerEu, kExtWavesPerEu))) void
 k_extend(ExtendArgs a) {
-  using Lt = ExtLayout<D>;
+  using Lt = ExtLayout<D, W>;
   constexpr int NKC = D / 32; // k chunks of S^T = K . Q^T
   constexpr int NDT = D / 16; // 16-channel tiles of O^T
-  constexpr int TQ = kExtRows / G;
+  constexpr int ROWS = 32 * W;
+  constexpr int TQ = ROWS / G;
+  constexpr int NB = Lt::NB;
   // Three block buffers: block b is read from buffer b % 3 while the copies
   // of blocks b + 1 and b + 2 land in the other two.  They are separate LDS
   // objects and the block loop below is unrolled by three, so every LDS
   // read names its buffer at compile time: the compiler then knows that the
   // copies in flight cannot alias it and does not wait for them.
-  __shared__ __attribute__((aligned(16))) uint16_t sk0[Lt::K_ELEMS], sk1[Lt::K_ELEMS], sk2[Lt::K_ELEMS];
-  __shared__ __attribute__((aligned(16))) uint16_t sv0[Lt::V_ELEMS], sv1[Lt::V_ELEMS], sv2[Lt::V_ELEMS];
+  // With two buffers block b + 1 alone is in flight.
+  __shared__ __attribute__((aligned(16))) uint16_t sk0[Lt::K_ELEMS], sk1[Lt::K_ELEMS], sk2[NB > 2 ? Lt::K_ELEMS : 8];
+  __shared__ __attribute__((aligned(16))) uint16_t sv0[Lt::V_ELEMS], sv1[Lt::V_ELEMS], sv2[NB > 2 ? Lt::V_ELEMS : 8];
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -494,17 +510,19 @@ k_extend(ExtendArgs a) {
   if (b_lo < b_hi) {
     block_ids(ids, a, b_lo);
     if constexpr (KV8) {
-      ext_load8<D>(kr, vr, a, kbase8, vbase8, ids, wave, lane);
-      ext_store8<D>(sk0, sv0, kr, vr, wave, lane);
+      ext_load8<D, W>(kr, vr, a, kbase8, vbase8, ids, wave, lane);
+      ext_store8<D, W>(sk0, sv0, kr, vr, wave, lane);
     } else {
-      ext_dma<D>(sk0, sv0, a, kbase, vbase, ids, wave, lane);
+      ext_dma<D, W>(sk0, sv0, a, kbase, vbase, ids, wave, lane);
       // the query loads, issued before this copy, have landed (said here, on
       // the only way into the loop, so that the compiler knows it)
       __builtin_amdgcn_s_waitcnt(kVmcntKeep<Lt::NK + Lt::NV>);
-      block_ids(ids, a, b_lo + 1);
-      ext_dma<D>(sk1, sv1, a, kbase, vbase, ids, wave, lane);
+      if constexpr (NB > 2) {
+        block_ids(ids, a, b_lo + 1);
+        ext_dma<D, W>(sk1, sv1, a, kbase, vbase, ids, wave, lane);
+      }
     }
-    block_ids(ids, a, KV8 ? b_lo + 1 : b_lo + 2);
+    block_ids(ids, a, KV8 || NB == 2 ? b_lo + 1 : b_lo + 2);
     // block b from buffers c; buffers n1 and n2 are those of blocks b + 1 and
     // b + 2 (an 8-bit store uses only two buffers)
     auto block = [&](int b, uint16_t *ck, uint16_t *cv, uint16_t *n1k, uint16_t *n1v,
@@ -531,16 +549,17 @@ k_extend(ExtendArgs a) {
       // block b has landed (every wave's copies; those of block b + 1, issued
       // later, may still be in flight) and every wave is done with block
       // b - 1, whose buffer the next copy overwrites
-      __builtin_amdgcn_s_waitcnt(KV8 ? 0 : kVmcntKeep<Lt::NK + Lt::NV>);
+      __builtin_amdgcn_s_waitcnt(KV8 ? 0 : kVmcntKeep<NB == 2 ? 0 : Lt::NK + Lt::NV>);
       lds_barrier();
       if ((b + 1) * BK > a.L) {
-        ext_zero_tail<D>(cv, b, a.L, tid);
+        ext_zero_tail<D, W>(cv, b, a.L, tid);
         lds_barrier();
       }
       if constexpr (KV8) {
-        if (b + 1 < b_hi) ext_load8<D>(kr, vr, a, kbase8, vbase8, ids, wave, lane); // stored after this block
+        if (b + 1 < b_hi) ext_load8<D, W>(kr, vr, a, kbase8, vbase8, ids, wave, lane); // stored after this block
       } else {
-        ext_dma<D>(n2k, n2v, a, kbase, vbase, ids, wave, lane);
+        if constexpr (NB > 2) ext_dma<D, W>(n2k, n2v, a, kbase, vbase, ids, wave, lane);
+        else ext_dma<D, W>(n1k, n1v, a, kbase, vbase, ids, wave, lane);
       }
       ext_block<D>(ck, cv, b, n, kg, a.scale_log2,
                    b * BK + BK - 1 > mask_from || b * BK < mask_below || masked_here, qf, first, lim,
@@ -548,11 +567,11 @@ k_extend(ExtendArgs a) {
                      if constexpr (KV8) {
                        if (b + 1 < b_hi) block_ids(ids, a, b + 2);
                      } else {
-                       block_ids(ids, a, b + 3);
+                       block_ids(ids, a, b + NB);
                      }
                    });
       if constexpr (KV8) { // a buffer every wave left by the top of this block
-        if (b + 1 < b_hi) ext_store8<D>(n1k, n1v, kr, vr, wave, lane);
+        if (b + 1 < b_hi) ext_store8<D, W>(n1k, n1v, kr, vr, wave, lane);
       }
     };
     if constexpr (KV8) {
@@ -560,6 +579,14 @@ k_extend(ExtendArgs a) {
         block(b, sk0, sv0, sk1, sv1, sk0, sv0);
         if (b + 1 < b_hi) block(b + 1, sk1, sv1, sk0, sv0, sk1, sv1);
       }
+    } else if constexpr (NB == 2) {
+      int b = b_lo;
+      for (; b + 1 < b_hi; b += 2) {
+        block(b, sk0, sv0, sk1, sv1, sk0, sv0);
+        block(b + 1, sk1, sv1, sk0, sv0, sk1, sv1);
+      }
+      if (b < b_hi) block(b, sk0, sv0, sk1, sv1, sk0, sv0);
+      __builtin_amdgcn_s_waitcnt(0); // no copy lands in LDS after the workgroup ends
     } else {
       // whole turns of the three buffers, then the rest: the loop's back
       // edge leaves every block of a turn behind it
@@ -583,7 +610,7 @@ k_extend(ExtendArgs a) {
       float l = sum_xrow16(l_run[cg]);
       l = sum_xrow32(l);
       if (!live[cg]) continue;
-      const int64_t row = slot * kExtRows + 32 * wave + 16 * cg + n;
+      const int64_t row = slot * ROWS + 32 * wave + 16 * cg + n;
       if (kg == 0) {
         a.part_m[row] = m_run[cg];
         a.part_l[row] = l;
@@ -619,26 +646,26 @@ k_extend(ExtendArgs a) {
 }
 
 // Merge of the split key range: one wave per (new token j, query head h),
-// lanes over channels.  Its partials are row (j % TQ) * G + h % G of the
+// lanes over channels.  Its partials are row (j % tq) * G + h % G of the
 // n_split slots of (query block j / TQ, KV head h / G):
 //   M = max m_s;  out = sum 2^(m_s - M) acc_s / sum 2^(m_s - M) l_s.
 template <int D, int G>
 __global__ __launch_bounds__(256) void k_extend_merge(ExtendArgs a) {
   constexpr int DPT = D / 64;
-  constexpr int TQ = kExtRows / G;
+  const int tq = a.rows / G;
   constexpr int U = 8;
   const int lane = threadIdx.x & 63;
   const int64_t r = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); // (j, h) row
   if (r >= (int64_t)a.n * a.hq) return;
   const int j = (int)(r / a.hq), h = (int)(r % a.hq);
   const int g = h / G;
-  const int64_t slot0 = ((int64_t)(j / TQ) * a.hkv + g) * a.n_split;
-  const int col = (j % TQ) * G + h % G;
+  const int64_t slot0 = ((int64_t)(j / tq) * a.hkv + g) * a.n_split;
+  const int col = (j % tq) * G + h % G;
   const int S = a.n_split;
   float mine = kNegInf, lmine = 0.f;
   if (lane < S) {
-    mine = a.part_m[(slot0 + lane) * kExtRows + col];
-    lmine = a.part_l[(slot0 + lane) * kExtRows + col];
+    mine = a.part_m[(slot0 + lane) * a.rows + col];
+    lmine = a.part_l[(slot0 + lane) * a.rows + col];
   }
   float big = mine;
 #pragma unroll
@@ -658,7 +685,7 @@ __global__ __launch_bounds__(256) void k_extend_merge(ExtendArgs a) {
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int sidx = min(s0 + u, S - 1);
-      const float *p = a.part_acc + ((slot0 + sidx) * kExtRows + col) * D + lane * DPT;
+      const float *p = a.part_acc + ((slot0 + sidx) * a.rows + col) * D + lane * DPT;
 #pragma unroll
       for (int q = 0; q < DPT; ++q) x[u][q] = p[q];
     }
@@ -674,26 +701,26 @@ __global__ __launch_bounds__(256) void k_extend_merge(ExtendArgs a) {
   for (int q = 0; q < DPT; ++q) op[q] = num[q] / den * a.out_scale;
 }
 
-template <int D> hipError_t extend_dispatch(int group, const ExtendArgs &a, hipStream_t s) {
-  const dim3 grid((unsigned)a.n_qblocks * (unsigned)a.hkv * (unsigned)a.n_split), block(kThreads);
-  if (a.kv8) {
-    switch (group) {
-    case 1: hipLaunchKernelGGL((k_extend<D, 1, true>), grid, block, 0, s, a); break;
-    case 2: hipLaunchKernelGGL((k_extend<D, 2, true>), grid, block, 0, s, a); break;
-    case 4: hipLaunchKernelGGL((k_extend<D, 4, true>), grid, block, 0, s, a); break;
-    case 8: hipLaunchKernelGGL((k_extend<D, 8, true>), grid, block, 0, s, a); break;
-    default: return hipErrorInvalidValue;
-    }
-    return hipGetLastError();
-  }
+template <int D, int W, bool KV8> hipError_t extend_dispatch(int group, const ExtendArgs &a, hipStream_t s) {
+  const dim3 grid((unsigned)a.n_qblocks * (unsigned)a.hkv * (unsigned)a.n_split), block(64 * W);
   switch (group) {
-  case 1: hipLaunchKernelGGL((k_extend<D, 1>), grid, block, 0, s, a); break;
-  case 2: hipLaunchKernelGGL((k_extend<D, 2>), grid, block, 0, s, a); break;
-  case 4: hipLaunchKernelGGL((k_extend<D, 4>), grid, block, 0, s, a); break;
-  case 8: hipLaunchKernelGGL((k_extend<D, 8>), grid, block, 0, s, a); break;
+  case 1: hipLaunchKernelGGL((k_extend<D, 1, W, KV8>), grid, block, 0, s, a); break;
+  case 2: hipLaunchKernelGGL((k_extend<D, 2, W, KV8>), grid, block, 0, s, a); break;
+  case 4: hipLaunchKernelGGL((k_extend<D, 4, W, KV8>), grid, block, 0, s, a); break;
+  case 8: hipLaunchKernelGGL((k_extend<D, 8, W, KV8>), grid, block, 0, s, a); break;
   default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
+}
+template <int D, bool KV8> hipError_t extend_dispatch_rows(int group, const ExtendArgs &a, hipStream_t s) {
+  switch (a.rows) {
+  case 256: return extend_dispatch<D, 8, KV8>(group, a, s);
+  case 128: return extend_dispatch<D, 4, KV8>(group, a, s);
+  case 64:
+    if constexpr (D == 128) return extend_dispatch<D, 2, KV8>(group, a, s);
+    return hipErrorInvalidValue; // (64 channels: 64 rows measured no faster than 128)
+  default: return hipErrorInvalidValue;
+  }
 }
 
 } // namespace
@@ -720,8 +747,8 @@ hipError_t launch_extend_merge(int d, int group, const ExtendArgs &a, hipStream_
 
 hipError_t launch_extend(int d, int group, const ExtendArgs &a, hipStream_t s) {
   if (a.n <= 0) return hipSuccess;
-  if (d == 128) return extend_dispatch<128>(group, a, s);
-  if (d == 64) return extend_dispatch<64>(group, a, s);
+  if (d == 128) return a.kv8 ? extend_dispatch_rows<128, true>(group, a, s) : extend_dispatch_rows<128, false>(group, a, s);
+  if (d == 64) return a.kv8 ? extend_dispatch_rows<64, true>(group, a, s) : extend_dispatch_rows<64, false>(group, a, s);
   return hipErrorInvalidValue;
 }
 

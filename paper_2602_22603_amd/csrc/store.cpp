@@ -815,6 +815,85 @@ void fill_dyn(sq_store *s, const Plan &plan, sq::DecodeDyn dyn[2], sq::MergeDyn 
   }
 }
 
+// How an extend call is cut into workgroups: rows query rows each (a tile of
+// 32 per wave), the key range of every (query block, KV head) over n_split of
+// them.
+struct ExtendPlan {
+  int32_t rows, n_qblocks, n_split, split_blocks;
+};
+
+// The cut with the least predicted time.  A CU holds one workgroup of 256
+// rows or two of 128 or 64 (their LDS).  64 keys against a workgroup were
+// measured on MI355X to take, at 128 channels, 2.35 us for 256 rows, 2.45 for
+// 128 beside another of the CU (1.52 alone) and 1.75 for 64; at 64 channels
+// 1.49 and 1.47 (0.95).  So wide tiles pay where rows fill them, narrow ones
+// where padding would: over 60.5K keys (32/8 heads of 128) 4 tokens take 87 us
+// at 256 rows, 54 at 128 and 48 at 64, 77 tokens 152, 127 and 146, 512 tokens
+// 577, 607 and 807.  The 64-row tile pays only when it holds the whole chunk
+// (a lone 128-row workgroup takes its keys faster than a 64-row one).  Splits
+// are chosen to fill whole rounds of the chip: a few workgroups past a round
+// cost another one (77 tokens at 128 rows: 127 us with 504 workgroups, 177
+// with 528), and every split writes and reads partial rows (512 tokens: 577
+// us at one round, 602 at two rounds of half the keys).
+ExtendPlan plan_extend(const sq_store *s, int64_t n, int64_t L, int64_t window) {
+  struct Tile {
+    int rows, per_cu;
+    double us, us_alone; // 64 keys, the CU full and one workgroup on it
+  };
+  static const Tile tiles128[] = {{256, 1, 2.35, 2.35}, {128, 2, 2.45, 1.52}, {64, 2, 1.75, 1.75}};
+  static const Tile tiles64[] = {{256, 1, 1.49, 1.49}, {128, 2, 1.47, 0.95}};
+  const Tile *tiles = s->D == 128 ? tiles128 : tiles64;
+  const int n_tiles = s->D == 128 && n * s->G <= 64 ? 3 : 2;
+  constexpr double kStart = 1.5;    // a workgroup's start-up, in blocks
+  constexpr double kMerge = 5.0;    // the merge launch, us
+  constexpr double kPartial = 5e6;  // partial bytes written and read per us
+  constexpr double kNarrow = 1.1;   // a narrow tile has to be this much better
+  constexpr int64_t kMinBlocks = 2; // key blocks per split
+  const int64_t hkv = s->cfg.num_kv_heads;
+  ExtendPlan best{};
+  double best_cost = 0;
+  for (int t = 0; t < n_tiles; ++t) {
+    const int64_t rows = tiles[t].rows, tq = rows / s->G;
+    const int64_t qb = (n + tq - 1) / tq;
+    int64_t kb = (L + sq::kExtKeys - 1) / sq::kExtKeys; // the last query block's key blocks
+    if (window > 0) // a query block's keys span at most W + TQ - 1 indices
+      kb = std::min<int64_t>(kb, (window + tq - 2) / sq::kExtKeys + 2);
+    // a query block sees this many key blocks fewer than the one after it
+    const double fewer = window > 0 ? 0.0 : (double)tq / sq::kExtKeys;
+    const int64_t wg = qb * hkv, slots = (int64_t)s->cus * tiles[t].per_cu;
+    const int64_t most = std::max<int64_t>(
+        1, std::min<int64_t>({64, kb / kMinBlocks, (int64_t)sq::kMaxItems * sq::kRows / rows / wg}));
+    for (int64_t r = 0; r <= 4; ++r) { // no split, then whole rounds of the CUs
+      const int64_t split = r == 0 ? 1 : std::min(most, std::max<int64_t>(1, s->cus * r / wg));
+      const int64_t all = wg * split, per = (kb + split - 1) / split;
+      // blocks of workgroup j, the longest first
+      auto blocks = [&](int64_t j) {
+        return std::min((double)per, std::max(0.0, (double)kb - (double)(j / (hkv * split)) * fewer)) + kStart;
+      };
+      double us; // of the longest chain
+      if (all <= slots) { // one round: CUs that hold two, then one
+        const double both = tiles[t].per_cu == 2 && all > s->cus ? blocks(s->cus) : 0.0;
+        us = both * tiles[t].us + (blocks(0) - both) * tiles[t].us_alone;
+      } else {
+        const double total = (double)hkv * qb * (kb - 0.5 * (double)(qb - 1) * fewer) + (double)all * kStart;
+        double chain = total / (double)slots;
+        for (int64_t k = 0; k * slots < all; ++k) { // k + 1 workgroups one after another
+          const bool half = k > 0 && tiles[t].per_cu == 2 && all - k * slots <= s->cus;
+          chain = std::max(chain, ((double)k + (half ? 0.6 : 1.0)) * blocks(k * slots));
+        }
+        us = chain * tiles[t].us;
+      }
+      if (split > 1) us += kMerge + (double)(n * s->cfg.num_q_heads * split) * (s->D + 2) * 8 / kPartial;
+      if (t > 0) us *= kNarrow;
+      if (best.rows == 0 || us < best_cost) {
+        best_cost = us;
+        best = {(int32_t)rows, (int32_t)qb, (int32_t)split, (int32_t)per};
+      }
+    }
+  }
+  return best;
+}
+
 // A small call's merge row lists in the arguments (MergeRows): the same
 // arithmetic the merge kernel does from the plan's tables, done here once.
 void fill_inline_rows(const sq_store *s, int batch, sq::MergeArgs *ma) {
@@ -2052,8 +2131,6 @@ sq_status sq_extend_attn_ex(sq_store *s, int32_t layer, sq_seq seq, int32_t n_ne
   a.n = n_new;
   a.hq = s->cfg.num_q_heads;
   a.hkv = s->cfg.num_kv_heads;
-  const int tq = sq::kExtRows / s->G;
-  a.n_qblocks = (n_new + tq - 1) / tq;
   a.scale_log2 = (float)((double)scale * 1.4426950408889634 * (double)s->k_scale(layer));
   a.sinks = o.sinks;
   a.window = o.window;
@@ -2064,24 +2141,11 @@ sq_status sq_extend_attn_ex(sq_store *s, int32_t layer, sq_seq seq, int32_t n_ne
   a.masked = sqn->n_masked > 0 ? 1 : 0;
   if (a.masked && o.window > 0)
     return fail(SQ_ERR_INVALID, "a window over a sequence with masked slots (compact it first)");
-  // A chunk too short to give every CU two rounds of workgroups (one fits a
-  // CU) splits the key range of each query block (at least 4 blocks of 64
-  // keys per split) and merges the partial rows in a second launch.
-  int64_t key_blocks = (sqn->length + sq::kExtKeys - 1) / sq::kExtKeys; // the last query block's
-  if (o.window > 0) // a query block's keys span at most W + TQ - 1 indices
-    key_blocks = std::min<int64_t>(key_blocks, ((int64_t)o.window + tq - 2) / sq::kExtKeys + 2);
-  const int64_t base_wg = (int64_t)a.n_qblocks * a.hkv;
-  const int64_t target = 2LL * s->cus;
-  int64_t split = 1;
-  if (base_wg < target) {
-    split = (target + base_wg - 1) / base_wg;
-    split = std::min<int64_t>(split, std::max<int64_t>(1, key_blocks / 4));
-    split = std::min<int64_t>(split, 64);
-    split = std::min<int64_t>(split, (int64_t)sq::kMaxItems * sq::kRows / sq::kExtRows / base_wg);
-    split = std::max<int64_t>(split, 1);
-  }
-  a.n_split = (int32_t)split;
-  a.split_blocks = (int32_t)((key_blocks + split - 1) / split);
+  const ExtendPlan ep = plan_extend(s, n_new, sqn->length, o.window);
+  a.rows = ep.rows;
+  a.n_qblocks = ep.n_qblocks;
+  a.n_split = ep.n_split;
+  a.split_blocks = ep.split_blocks;
   a.part_m = s->part_m;
   a.part_l = s->part_l;
   a.part_acc = s->part_acc;

@@ -125,6 +125,40 @@ def test_extend_key_block_counts(sq, hq, hkv, d, length):
     assert err <= TOL
 
 
+@pytest.mark.parametrize("hq,hkv,d", [(8, 2, 128), (8, 1, 128), (8, 2, 64)])
+@pytest.mark.parametrize("rows", [63, 64, 65, 127, 129, 257])
+@pytest.mark.parametrize("prefix", [0, 70, 190])
+def test_extend_row_tile_edges(sq, hq, hkv, d, rows, prefix):
+    """Chunks whose query rows (tokens x heads per KV head) just fill, or just
+    pass, the 64- and 128-row tiles that short chunks run on, against odd and
+    even counts of key blocks (those tiles alternate two block buffers)."""
+    n = -(-rows // (hq // hkv))
+    tw = _twin(sq, hq, hkv, d, prefix + n, seed=190 + rows + prefix)
+    a = tw.create()
+    if prefix:
+        tw.append(a, prefix)
+    tw.append(a, n)
+    err = _extend_error(tw, a, n)
+    print(f"extend hq={hq} hkv={hkv} d={d} prefix={prefix} n={n}: max abs err {err:.2e}")
+    assert err <= TOL
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_extend_wide_tile_key_block_counts(sq, d):
+    """A 4096-token chunk with no prefix runs on 256-row tiles (64 tokens of 4
+    heads): its query blocks see 1, 2, .. 64 key blocks, so every count of
+    whole buffer turns and of blocks left over occurs; two rows of each of the
+    first nine and last three query blocks are checked."""
+    n = 4096
+    tw = _twin(sq, 32, 8, d, n, seed=211)
+    a = tw.create()
+    tw.append(a, n)
+    blocks = list(range(9)) + [61, 62, 63]
+    err = _extend_error(tw, a, n, pairs=[(64 * b + j, (b + j) % 8) for b in blocks for j in (0, 63)])
+    print(f"extend d={d} n={n}: max abs err {err:.2e}")
+    assert err <= TOL
+
+
 @pytest.mark.parametrize("hq,hkv,d", [(32, 8, 128), (8, 2, 64)])
 def test_extend_scores_far_above_the_running_reference(sq, hq, hkv, d):
     """Keys scaled by 16 and by 64 (exact in bf16) after ordinary ones: a
