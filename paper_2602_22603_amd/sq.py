@@ -195,8 +195,12 @@ def _ptr(t):
 
 def _stream(stream):
     if stream is None:
+        # the current stream's handle without a Stream object around it: 0.4
+        # against 3.0 us, a fifth of a small decode call's host time
         import torch
-        return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+        if not torch.cuda.is_initialized():
+            torch.cuda.init()
+        return C.c_void_p(torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice()))
     if isinstance(stream, int):
         return C.c_void_p(stream)
     return C.c_void_p(stream.cuda_stream)
@@ -289,7 +293,7 @@ class Store:
             raise SqError(ERR_INVALID, f"{what} must be a torch tensor")
         if t.dtype != dtype:
             raise SqError(ERR_INVALID, f"{what} must be {dtype}, got {t.dtype}")
-        if tuple(t.shape) != tuple(shape):
+        if t.shape != shape:
             raise SqError(ERR_INVALID, f"{what} must have shape {tuple(shape)}, got {tuple(t.shape)}")
         if not t.is_contiguous():
             raise SqError(ERR_INVALID, f"{what} must be contiguous")
