@@ -1,6 +1,6 @@
 // fp8.hpp - the 8-bit E4M3 KV-cache code on gfx950: quantisation of a float
-// (in software, exact) and conversion of stored codes to bf16 for the
-// matrix cores (the native conversion instruction).
+// and conversion of stored codes to bf16 for the matrix cores (the native
+// conversion instructions).
 // Internal to libsq.
 //
 // E4M3 (the OCP 8-bit format, gfx950's native FP8): sign, 4 exponent bits
@@ -14,29 +14,18 @@
 
 namespace sq {
 
-// The code nearest to y (ties to the even code), magnitudes >= 448
-// saturating to 448, the sign of y kept.  y must not be NaN.
-__device__ inline uint32_t e4m3_encode(float y) {
-  const uint32_t u = __float_as_uint(y);
-  const uint32_t sign = (u >> 24) & 0x80u;
-  const float a = __uint_as_float(u & 0x7fffffffu);
-  uint32_t code;
-  if (a >= 448.f) {
-    code = 0x7eu;
-  } else {
-    const int e = (int)((u >> 23) & 0xffu) - 127;
-    if (e >= -6) { // normal: round the 23-bit mantissa to 3 bits
-      const uint32_t m23 = u & 0x7fffffu;
-      uint32_t m3 = m23 >> 20;
-      const uint32_t rem = m23 & 0xfffffu;
-      m3 += (rem > 0x80000u || (rem == 0x80000u && (m3 & 1u))) ? 1u : 0u;
-      code = ((uint32_t)(e + 7) << 3) + m3; // m3 == 8 carries into the exponent
-    } else { // subnormal steps of 2^-9 (the product is exact; rint rounds to even)
-      code = (uint32_t)__builtin_rintf(a * 512.f);
-    }
-  }
-  return code | sign;
+// The codes of y0 and y1 (bits 0-7 and 8-15): the nearest (ties to the even
+// code), magnitudes >= 448 saturating to 448, the sign kept.  The conversion
+// instruction rounds so but does not saturate, so the values are clamped in
+// front of it.  Neither may be NaN.  With the code put together from the
+// float's fields instead, appending 4096 tokens of 12 layers took 76 us; 60
+// with the instruction.
+__device__ inline uint32_t e4m3_encode2(float y0, float y1) {
+  const float c0 = __builtin_amdgcn_fmed3f(y0, -448.f, 448.f);
+  const float c1 = __builtin_amdgcn_fmed3f(y1, -448.f, 448.f);
+  return (uint32_t)__builtin_amdgcn_cvt_pk_fp8_f32(c0, c1, 0, false) & 0xffffu;
 }
+__device__ inline uint32_t e4m3_encode(float y) { return e4m3_encode2(y, 0.f) & 0xffu; }
 
 // Four codes (bytes of w, lowest first) as four bf16 values (two 32-bit
 // words, lowest first).  Exact for every finite code.

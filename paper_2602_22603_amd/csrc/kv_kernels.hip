@@ -15,6 +15,8 @@
 #include "fp8.hpp"
 #include "kv_args.hpp"
 
+#include <type_traits>
+
 namespace sq {
 namespace {
 
@@ -33,138 +35,163 @@ __device__ inline uint16_t *v_chunk_w(const Pools &p, int layer, int page, int h
   return p.v + layer * p.layer_stride + (int64_t)page * p.page_stride + head * p.head_stride;
 }
 
-// ---------------------------------------------------------------------------
-// Append: one block per (page touched, layer * Hkv + head).  New tokens come
-// token-major [NL][n_total][Hkv][D]; K rows are copied as 16-byte units, V is
-// transposed through LDS when a whole page is written and scattered per
-// element when only some slots of a page are (the other slots of that page
-// already hold earlier tokens of the sequence).
-template <int D>
-__global__ __launch_bounds__(256) void k_append(Pools p, AppendArgs a,
-                                                const uint16_t *__restrict__ kn,
-                                                const uint16_t *__restrict__ vn) {
-  constexpr int U = D / 8; // 16-byte units per row
-  __shared__ uint16_t tile[P][D + 8];
-  const int pi = blockIdx.x;
-  const int lh = blockIdx.y;
-  const int layer = lh / p.hkv;
-  const int head = lh % p.hkv;
-  const int page = a.page_ids[pi];
-  const int s_begin = pi == 0 ? a.slot0 : 0;
-  const int t_begin = pi == 0 ? 0 : pi * P - a.slot0; // launch-local token of s_begin
-  int s_end = s_begin + (a.n_tok - t_begin);
-  if (s_end > P) s_end = P;
-  const int ns = s_end - s_begin;
-  const int64_t tok_stride = (int64_t)p.hkv * D;
-  const int64_t src0 = ((int64_t)layer * a.n_total + a.tok0 + t_begin) * tok_stride + head * D;
-
-  uint16_t *kd = k_chunk_w(p, layer, page, head);
-  for (int idx = threadIdx.x; idx < ns * U; idx += blockDim.x) {
-    const int j = idx / U, u = idx % U;
-    const uint4 val = *(reinterpret_cast<const uint4 *>(kn + src0 + j * tok_stride) + u);
-    *(reinterpret_cast<uint4 *>(kd + (s_begin + j) * D) + u) = val;
-  }
-
-  uint16_t *vd = v_chunk_w(p, layer, page, head);
-  if (ns == P) {
-    for (int idx = threadIdx.x; idx < P * U; idx += blockDim.x) {
-      const int j = idx / U, u = idx % U;
-      const uint4 val = *(reinterpret_cast<const uint4 *>(vn + src0 + j * tok_stride) + u);
-      *reinterpret_cast<uint4 *>(&tile[j][u * 8]) = val;
-    }
-    __syncthreads();
-    for (int idx = threadIdx.x; idx < D * 2; idx += blockDim.x) {
-      const int d = idx >> 1, h = idx & 1;
-      uint32_t w[4];
-#pragma unroll
-      for (int e = 0; e < 4; ++e)
-        w[e] = (uint32_t)tile[h * 8 + 2 * e][d] | ((uint32_t)tile[h * 8 + 2 * e + 1][d] << 16);
-      *reinterpret_cast<uint4 *>(vd + d * P + h * 8) = make_uint4(w[0], w[1], w[2], w[3]);
-    }
-  } else {
-    for (int idx = threadIdx.x; idx < ns * D; idx += blockDim.x) {
-      const int j = idx % ns, d = idx / ns;
-      vd[d * P + s_begin + j] = vn[src0 + j * tok_stride + d];
-    }
-  }
-
-  if (lh == 0) {
-    for (int j = threadIdx.x; j < ns; j += blockDim.x)
-      p.pos[(int64_t)page * P + s_begin + j] = a.pos0 + t_begin + j;
-    if (threadIdx.x == 0 && pi >= a.new_from) a.pt_row[a.pt_first + pi] = page;
-  }
+// Element E of the pools (bf16 bits, or E4M3 bytes): the chunk of one
+// (layer, page, head), strides counted in elements.
+template <class E> __device__ inline E *chunk_of(uint16_t *pool, const Pools &p, int layer, int page,
+                                                 int head) {
+  return reinterpret_cast<E *>(pool) + layer * p.layer_stride + (int64_t)page * p.page_stride +
+         head * p.head_stride;
 }
 
-// The same for an 8-bit store: each bf16 value x becomes the E4M3 code of
+// Non-temporal 16- and 8-byte moves.
+typedef uint32_t nt4_t __attribute__((ext_vector_type(4)));
+typedef uint32_t nt2_t __attribute__((ext_vector_type(2)));
+template <bool NT> __device__ inline uint4 load16(const void *src) {
+  if constexpr (!NT) return *static_cast<const uint4 *>(src);
+  const nt4_t x = __builtin_nontemporal_load(static_cast<const nt4_t *>(src));
+  return make_uint4(x.x, x.y, x.z, x.w);
+}
+__device__ inline void store_nt(void *dst, uint4 x) {
+  __builtin_nontemporal_store(nt4_t{x.x, x.y, x.z, x.w}, static_cast<nt4_t *>(dst));
+}
+__device__ inline void store_nt(void *dst, uint2 x) {
+  __builtin_nontemporal_store(nt2_t{x.x, x.y}, static_cast<nt2_t *>(dst));
+}
+
+// ---------------------------------------------------------------------------
+// Append.  New tokens come token-major [NL][n_total][Hkv][D]; K rows are
+// copied as 16-byte units, V is transposed through LDS when a whole page is
+// written and scattered per element when only some slots of a page are (the
+// other slots of that page already hold earlier tokens of the sequence).  In
+// an 8-bit store each bf16 value x becomes the E4M3 code of
 // float(x) * (1 / scale) of its layer (K and V scales apart).
+//
+// The kernel is bound by HBM: each byte is read once and written once.  A
+// workgroup takes one 8 KB unit of work (a page of 128 channels, two of 64)
+// with every load in flight before the first store; groups of twice that were
+// 1-4% slower.  Pages are stored non-temporally, so that they do not push the
+// source out of the caches on their way: 8192 tokens of 24 layers (8 heads of
+// 128) 322 -> 294 us, 8000 tokens of 2 heads 89 -> 65 us.  The source is
+// loaded non-temporally too (NTL) when it is larger than the 256 MB memory-side
+// cache, so that little of it can be there: 294 -> 280 us (5.8 TB/s); a smaller
+// one may still be there from the projection that wrote it (3000 tokens of 12
+// layers, 147 MB, just read: 48 us, with non-temporal loads 51).
 __device__ inline float bf16_val(uint16_t b) { return __uint_as_float((uint32_t)b << 16); }
 __device__ inline uint2 quant8(uint4 w, float inv) { // 8 bf16 -> 8 codes
   const uint32_t x[4] = {w.x, w.y, w.z, w.w};
-  uint32_t c[8];
+  uint32_t c[4];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    c[2 * i] = e4m3_encode(__uint_as_float(x[i] << 16) * inv);
-    c[2 * i + 1] = e4m3_encode(__uint_as_float(x[i] & 0xffff0000u) * inv);
-  }
-  return make_uint2(c[0] | c[1] << 8 | c[2] << 16 | c[3] << 24,
-                    c[4] | c[5] << 8 | c[6] << 16 | c[7] << 24);
+  for (int i = 0; i < 4; ++i)
+    c[i] = e4m3_encode2(__uint_as_float(x[i] << 16) * inv, __uint_as_float(x[i] & 0xffff0000u) * inv);
+  return make_uint2(c[0] | c[1] << 16, c[2] | c[3] << 16);
 }
 
-template <int D>
-__global__ __launch_bounds__(256) void k_append8(Pools p, AppendArgs a,
-                                                 const uint16_t *__restrict__ kn,
-                                                 const uint16_t *__restrict__ vn) {
-  constexpr int U = D / 8; // 8-element units per row
-  __shared__ uint16_t tile[P][D + 8];
-  const int pi = blockIdx.x;
-  const int lh = blockIdx.y;
-  const int layer = lh / p.hkv;
-  const int head = lh % p.hkv;
-  const float inv_k = p.scales[4 * layer + 2], inv_v = p.scales[4 * layer + 3];
-  const int page = a.page_ids[pi];
-  const int s_begin = pi == 0 ? a.slot0 : 0;
-  const int t_begin = pi == 0 ? 0 : pi * P - a.slot0;
-  int s_end = s_begin + (a.n_tok - t_begin);
-  if (s_end > P) s_end = P;
-  const int ns = s_end - s_begin;
-  const int64_t tok_stride = (int64_t)p.hkv * D;
-  const int64_t src0 = ((int64_t)layer * a.n_total + a.tok0 + t_begin) * tok_stride + head * D;
-  const int64_t chunk = layer * p.layer_stride + (int64_t)page * p.page_stride + head * p.head_stride;
+template <int D> constexpr int kAppendGroup = 128 / D; // pages of one workgroup
 
-  uint8_t *kd = reinterpret_cast<uint8_t *>(p.k) + chunk;
-  for (int idx = threadIdx.x; idx < ns * U; idx += blockDim.x) {
-    const int j = idx / U, u = idx % U;
-    const uint4 val = *(reinterpret_cast<const uint4 *>(kn + src0 + j * tok_stride) + u);
-    *reinterpret_cast<uint2 *>(kd + (s_begin + j) * D + 8 * u) = quant8(val, inv_k);
+template <int D, class E, bool NTL>
+__global__ __launch_bounds__(256) void k_append(Pools p, AppendArgs a,
+                                                const uint16_t *__restrict__ kn,
+                                                const uint16_t *__restrict__ vn) {
+  constexpr bool KV8 = sizeof(E) == 1;
+  constexpr int U = D / 8;                       // 16-byte units per source row
+  constexpr int NPG = kAppendGroup<D>;           // pages per workgroup
+  constexpr int PT = P * U;                      // threads that load a page's K (and V)
+  __shared__ uint16_t tile[NPG][P][D + 8];
+  const int p0 = blockIdx.x * NPG;
+  const int layer = blockIdx.y / p.hkv, head = blockIdx.y % p.hkv;
+  float inv_k = 1.f, inv_v = 1.f;
+  if constexpr (KV8) {
+    inv_k = p.scales[4 * layer + 2];
+    inv_v = p.scales[4 * layer + 3];
   }
-
-  uint8_t *vd = reinterpret_cast<uint8_t *>(p.v) + chunk;
-  if (ns == P) {
-    for (int idx = threadIdx.x; idx < P * U; idx += blockDim.x) {
-      const int j = idx / U, u = idx % U;
-      const uint4 val = *(reinterpret_cast<const uint4 *>(vn + src0 + j * tok_stride) + u);
-      *reinterpret_cast<uint4 *>(&tile[j][u * 8]) = val;
+  const int64_t tok_stride = (int64_t)p.hkv * D;
+  const uint16_t *ks = kn + ((int64_t)layer * a.n_total + a.tok0) * tok_stride + head * D;
+  const uint16_t *vs = vn + ((int64_t)layer * a.n_total + a.tok0) * tok_stride + head * D;
+  auto kpage = [&](int i) { return chunk_of<E>(p.k, p, layer, a.page_ids[p0 + i], head); };
+  auto vpage = [&](int i) { return chunk_of<E>(p.v, p, layer, a.page_ids[p0 + i], head); };
+  // launch-local token of slot 0 of page p0
+  const int tok = p0 * P - a.slot0;
+  // N whole pages from page p0 + i0 on: all loads in flight together
+  auto move_whole = [&](auto n_pages, int i0) {
+    constexpr int N = decltype(n_pages)::value;
+    constexpr int NR = (N * PT + 255) / 256; // units per thread
+    const int t0 = tok + i0 * P;
+    uint4 kr[NR], vr[NR];
+#pragma unroll
+    for (int r = 0; r < NR; ++r) {
+      const int idx = r * 256 + threadIdx.x;
+      if (N * PT < 256 && idx >= N * PT) break;
+      const int64_t src = (t0 + idx / U) * tok_stride + idx % U * 8;
+      kr[r] = load16<NTL>(ks + src);
+      vr[r] = load16<NTL>(vs + src);
+    }
+#pragma unroll
+    for (int r = 0; r < NR; ++r) {
+      const int idx = r * 256 + threadIdx.x;
+      if (N * PT < 256 && idx >= N * PT) break;
+      *reinterpret_cast<uint4 *>(&tile[idx / PT][idx / U % P][idx % U * 8]) = vr[r];
+    }
+#pragma unroll
+    for (int r = 0; r < NR; ++r) {
+      const int idx = r * 256 + threadIdx.x;
+      if (N * PT < 256 && idx >= N * PT) break;
+      E *kd = kpage(i0 + idx / PT) + idx % PT * 8;
+      if constexpr (KV8) store_nt(kd, quant8(kr[r], inv_k));
+      else store_nt(kd, kr[r]);
     }
     __syncthreads();
-    for (int idx = threadIdx.x; idx < D * 2; idx += blockDim.x) {
-      const int d = idx >> 1, h = idx & 1;
-      uint32_t w[2] = {0u, 0u};
 #pragma unroll
-      for (int e = 0; e < 8; ++e)
-        w[e >> 2] |= e4m3_encode(bf16_val(tile[h * 8 + e][d]) * inv_v) << (8 * (e & 3));
-      *reinterpret_cast<uint2 *>(vd + d * P + h * 8) = make_uint2(w[0], w[1]);
+    for (int r = 0; r < NR; ++r) {
+      const int idx = r * 256 + threadIdx.x;
+      if (N * PT < 256 && idx >= N * PT) break;
+      const int i = idx / PT, d = idx % PT / 2, h = idx & 1;
+      uint32_t w[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        w[e] = (uint32_t)tile[i][h * 8 + 2 * e][d] | (uint32_t)tile[i][h * 8 + 2 * e + 1][d] << 16;
+      const uint4 o = make_uint4(w[0], w[1], w[2], w[3]);
+      E *vd = vpage(i0 + i) + d * P + h * 8;
+      if constexpr (KV8) store_nt(vd, quant8(o, inv_v));
+      else store_nt(vd, o);
     }
+  };
+  if (tok >= 0 && tok + NPG * P <= a.n_tok) {
+    move_whole(std::integral_constant<int, NPG>(), 0);
   } else {
-    for (int idx = threadIdx.x; idx < ns * D; idx += blockDim.x) {
-      const int j = idx % ns, d = idx / ns;
-      vd[d * P + s_begin + j] = (uint8_t)e4m3_encode(bf16_val(vn[src0 + j * tok_stride + d]) * inv_v);
+    const int n_pg = min(NPG, a.n_pages - p0);
+    for (int i = 0; i < n_pg; ++i) {
+      const int t0 = tok + i * P; // token of the page's slot 0
+      const int s0 = max(0, -t0), ns = min(P, a.n_tok - t0) - s0;
+      if (ns == P) {
+        move_whole(std::integral_constant<int, 1>(), i);
+        __syncthreads(); // the next page reuses the tile
+        continue;
+      }
+      const int64_t src = (t0 + s0) * tok_stride;
+      E *kd = kpage(i) + s0 * D;
+      for (int idx = threadIdx.x; idx < ns * U; idx += 256) {
+        const int j = idx / U, u = idx % U;
+        const uint4 val = *reinterpret_cast<const uint4 *>(ks + src + j * tok_stride + 8 * u);
+        if constexpr (KV8) *reinterpret_cast<uint2 *>(kd + j * D + 8 * u) = quant8(val, inv_k);
+        else *reinterpret_cast<uint4 *>(kd + j * D + 8 * u) = val;
+      }
+      E *vd = vpage(i) + s0;
+      for (int idx = threadIdx.x; idx < ns * D; idx += 256) {
+        const int d = idx % D, j = idx / D;
+        const uint16_t val = vs[src + j * tok_stride + d];
+        if constexpr (KV8) vd[d * P + j] = (E)e4m3_encode(bf16_val(val) * inv_v);
+        else vd[d * P + j] = val;
+      }
     }
   }
 
-  if (lh == 0) {
-    for (int j = threadIdx.x; j < ns; j += blockDim.x)
-      p.pos[(int64_t)page * P + s_begin + j] = a.pos0 + t_begin + j;
-    if (threadIdx.x == 0 && pi >= a.new_from) a.pt_row[a.pt_first + pi] = page;
+  if (layer == 0 && head == 0) {
+    for (int idx = threadIdx.x; idx < NPG * P; idx += 256) {
+      const int t = tok + idx;
+      if (t >= 0 && t < a.n_tok) p.pos[(int64_t)a.page_ids[p0 + idx / P] * P + idx % P] = a.pos0 + t;
+    }
+    const int pi = p0 + threadIdx.x;
+    if (threadIdx.x < NPG && pi < a.n_pages && pi >= a.new_from) a.pt_row[a.pt_first + pi] = a.page_ids[pi];
   }
 }
 
@@ -233,14 +260,6 @@ __global__ __launch_bounds__(256) void k_copy_i32(int32_t *dst, const int32_t *s
 __global__ __launch_bounds__(256) void k_fill_i32(int32_t *dst, int32_t value, int32_t n) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) dst[i] = value;
-}
-
-// Element E of the pools (bf16 bits, or E4M3 bytes): the chunk of one
-// (layer, page, head), strides counted in elements.
-template <class E> __device__ inline E *chunk_of(uint16_t *pool, const Pools &p, int layer, int page,
-                                                 int head) {
-  return reinterpret_cast<E *>(pool) + layer * p.layer_stride + (int64_t)page * p.page_stride +
-         head * p.head_stride;
 }
 
 // Whole-page copy (every layer and head, K, V and pos): the fork's tail page.
@@ -652,21 +671,31 @@ __global__ __launch_bounds__(256) void k_evict_inplace(Pools p, InplaceArgs a) {
 } // namespace
 
 // ---------------------------------------------------------------------------
+namespace {
+constexpr int64_t kMemSideCache = 256ll << 20;
+
+template <int D, class E>
+hipError_t append_dispatch(const Pools &p, const AppendArgs &a, const uint16_t *kn,
+                           const uint16_t *vn, hipStream_t s) {
+  const dim3 grid((a.n_pages + kAppendGroup<D> - 1) / kAppendGroup<D>, p.nl * p.hkv), block(256);
+  const bool beyond = (int64_t)p.nl * a.n_total * p.hkv * D * 4 > kMemSideCache; // K and V
+  if (beyond)
+    hipLaunchKernelGGL((k_append<D, E, true>), grid, block, 0, s, p, a, kn, vn);
+  else
+    hipLaunchKernelGGL((k_append<D, E, false>), grid, block, 0, s, p, a, kn, vn);
+  return hipGetLastError();
+}
+} // namespace
+
 hipError_t launch_append(const Pools &p, const AppendArgs &a, const void *k_new,
                          const void *v_new, hipStream_t s) {
-  dim3 grid(a.n_pages, p.nl * p.hkv);
   const auto *kn = static_cast<const uint16_t *>(k_new);
   const auto *vn = static_cast<const uint16_t *>(v_new);
-  if (p.kv8) {
-    if (p.d == 128)
-      hipLaunchKernelGGL(k_append8<128>, grid, dim3(256), 0, s, p, a, kn, vn);
-    else
-      hipLaunchKernelGGL(k_append8<64>, grid, dim3(256), 0, s, p, a, kn, vn);
-  } else if (p.d == 128)
-    hipLaunchKernelGGL(k_append<128>, grid, dim3(256), 0, s, p, a, kn, vn);
-  else
-    hipLaunchKernelGGL(k_append<64>, grid, dim3(256), 0, s, p, a, kn, vn);
-  return hipGetLastError();
+  if (p.kv8)
+    return p.d == 128 ? append_dispatch<128, uint8_t>(p, a, kn, vn, s)
+                      : append_dispatch<64, uint8_t>(p, a, kn, vn, s);
+  return p.d == 128 ? append_dispatch<128, uint16_t>(p, a, kn, vn, s)
+                    : append_dispatch<64, uint16_t>(p, a, kn, vn, s);
 }
 
 hipError_t launch_append_batch(const Pools &p, const AppendBatchArgs &a, const void *k_new,

@@ -254,3 +254,39 @@ def test_merge_row_lists_in_arguments_and_from_the_plan(sq, hq, hkv):
     for seqs in ([a], [b], [a, b], [c, a], [a, b, c]):
         errs, _ = _check(t, seqs)
         print(f"hq={hq} hkv={hkv} batch {len(seqs)}:", {m: f"{e:.1e}" for m, e in errs.items()})
+
+
+@pytest.mark.parametrize("d,kv8", [(128, False), (64, False), (128, True)])
+def test_append_larger_than_the_memory_side_cache(sq, d, kv8):
+    """An append whose source exceeds 256 MB (non-temporal loads) stores what
+    the same tokens stored in halves do (ordinary loads), bit for bit, on both
+    sides of the line and from a ragged slot on."""
+    import torch
+    nl, hkv, base = 8, 8, 5
+    for n in ((256 << 20) // (nl * hkv * d * 4), (256 << 20) // (nl * hkv * d * 4) + 1):
+        gen = torch.Generator(device="cuda")
+        gen.manual_seed(n)
+        k, v = (torch.randn((nl, base + n, hkv, d), generator=gen, device="cuda").to(torch.bfloat16)
+                for _ in range(2))
+        pages = (base + n) // 16 + 2
+        pools = []
+        for cuts in ((0, base, base + n), (0, base, base + n // 2, base + n)):
+            s = sq.Store(nl, hkv, hkv, d, pages, 1, pages, device="cuda",
+                         kv_scales=[[0.02, 0.03]] * nl if kv8 else None)
+            a = s.seq_create()
+            for lo, hi in zip(cuts, cuts[1:]):
+                s.append(a, k[:, lo:hi].contiguous(), v[:, lo:hi].contiguous())
+            assert s.page_table(a) == list(range((base + n + 15) // 16))
+            torch.cuda.synchronize()
+            full = (base + n) // 16
+            tail = (base + n) % 16
+            pools.append((s.k_pool[:, :, :full].clone(), s.v_pool[:, :, :full].clone(), s.pos_pool[:full].clone(),
+                          s.k_pool[:, :, full, :tail].clone(), s.v_pool[:, :, full, :, :tail].clone()))
+            s.close()
+        for x, y in zip(*pools):
+            assert torch.equal(x, y)
+        if not kv8:
+            want = k[:, :full * 16].view(nl, full, 16, hkv, d).permute(0, 3, 1, 2, 4)
+            assert torch.equal(pools[0][0].view(torch.int16).reshape(want.shape), want.contiguous().view(torch.int16))
+            want = v[:, :full * 16].view(nl, full, 16, hkv, d).permute(0, 3, 1, 4, 2)
+            assert torch.equal(pools[0][1].view(torch.int16).reshape(want.shape), want.contiguous().view(torch.int16))

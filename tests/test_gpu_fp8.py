@@ -116,6 +116,31 @@ def test_appended_codes_are_the_oracle_quantisation(sq, d):
     s.close()
 
 
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("scale", [1.0, 0.011, 300.0])
+def test_every_bf16_value_is_quantised_as_the_oracle_does(sq, d, scale):
+    """All 65,282 bf16 values that are not NaN, infinities among them, as K
+    and (reversed) as V: whole pages, and single slots of the first and last."""
+    import torch
+    bits = np.arange(65536, dtype=np.uint32) << 16
+    vals = bits.view(np.float32)
+    vals = vals[~np.isnan(vals)]
+    n = -(-len(vals) // (2 * d))
+    x = np.resize(vals, n * 2 * d).reshape(1, n, 2, d)
+    y = x[:, :, ::-1, ::-1].copy()
+    s = sq.Store(1, 4, 2, d, n // 16 + 3, 2, n // 16 + 3, device="cuda", kv_scales=[[scale, scale]])
+    a = s.seq_create()
+    kb, vb = (torch.from_numpy(z).to(torch.bfloat16).to("cuda") for z in (x, y))
+    for lo, hi in ((0, 5), (5, n)):
+        s.append(a, kb[:, lo:hi].contiguous(), vb[:, lo:hi].contiguous())
+    torch.cuda.synchronize()
+    kc, vc = _codes(s, a, 0)
+    with np.errstate(all="ignore"):
+        assert np.array_equal(kc, of8.quantize(x[0], scale))
+        assert np.array_equal(vc, of8.quantize(y[0], scale))
+    s.close()
+
+
 @pytest.mark.parametrize("hq,hkv,d", [(32, 8, 128), (8, 2, 64), (64, 8, 64), (4, 4, 128)])
 def test_fp8_decode_fork_evict(sq, hq, hkv, d):
     """Main thread, its fork (aligned and mid-page), eviction while the
