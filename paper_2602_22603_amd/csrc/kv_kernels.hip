@@ -379,110 +379,161 @@ __global__ __launch_bounds__(256) void k_write_ids(int32_t *dst, NewIds ids, int
   if (i < n) dst[i] = new_page_id(ids, i);
 }
 
-// One destination page's sources, staged: each slot's source page id and
-// slot (LDS, written by the first P threads from src_of and the page-table
-// row, which still holds the old ids), and the distinct
-// source pages in order, which every thread finds itself from LDS (the kept
-// tokens are in old order, and a page list holds a page once, so the source
-// page changes exactly where the id does).
-constexpr int kMaxStaged = 4; // source pages of one destination page staged whole
-struct PageSources {
-  int nv;                  // valid slots
-  int nu;                  // distinct source pages (may exceed kMaxStaged)
-  int u0, u1, u2, u3;      // their ids, the first kMaxStaged of them (scalars,
-                           // so that nothing is indexed at run time)
-  __device__ int up(int u) const { return u == 0 ? u0 : u == 1 ? u1 : u == 2 ? u2 : u3; }
-};
-static_assert(kMaxStaged == 4, "PageSources holds four staged pages");
+// ---------------------------------------------------------------------------
+// The move of one destination page of one or more KV rows (row = layer * Hkv
+// + head; the rows of a pool are head_stride apart).
+//
+// Almost every page of a compacted tail is a run: its P kept tokens are P
+// consecutive old tokens, since spans and the runs between them are long.
+// They lie in slots [slot0, P) of one old page and [0, slot0) of the next,
+// so the destination's K is P * D consecutive elements of the two, and a
+// 16-byte unit of its V^T is 16 bytes of two neighbouring units of a
+// channel's row, put together by a funnel shift that is the same for the
+// whole workgroup.  Nothing passes through LDS and nothing waits but the
+// stores for the loads: one unit of K and one of V per thread.  Bound by HBM:
+// 20K tokens of 6 layers moved (8 heads of 128, 0.98 GB read and written)
+// 216 -> 181 us a call (with two units per thread 194, with four 203), 36K
+// tokens of 4 layers of an 8-bit store 207 -> 97 us, both against staging the
+// source pages' V^T in LDS and putting each element together from there.
+template <int D, class E> constexpr int kPageUnits = P * D * (int)sizeof(E) / 16;
+template <int D, class E> constexpr int kGatherRows = 256 / kPageUnits<D, E>; // rows per workgroup
 
-__device__ inline void load_sources(const int32_t *src_of, const int32_t *pt_row, int t0, int nv,
-                                    int *spage, int *sslot) {
-  if ((int)threadIdx.x < nv) {
-    const int src = src_of[t0 + threadIdx.x];
-    spage[threadIdx.x] = pt_row[src / P];
-    sslot[threadIdx.x] = src % P;
+// Bytes [sh, sh + 16) of lo | hi (sh < 16, uniform).
+__device__ inline uint4 funnel16(uint4 lo, uint4 hi, int sh) {
+  const int b = sh & 3;
+  auto pick = [&](uint32_t w0, uint32_t w1, uint32_t w2, uint32_t w3, uint32_t w4) {
+    return make_uint4(__builtin_amdgcn_alignbyte(w1, w0, b), __builtin_amdgcn_alignbyte(w2, w1, b),
+                      __builtin_amdgcn_alignbyte(w3, w2, b), __builtin_amdgcn_alignbyte(w4, w3, b));
+  };
+  switch (sh >> 2) {
+  case 0: return pick(lo.x, lo.y, lo.z, lo.w, hi.x);
+  case 1: return pick(lo.y, lo.z, lo.w, hi.x, hi.y);
+  case 2: return pick(lo.z, lo.w, hi.x, hi.y, hi.z);
+  default: return pick(lo.w, hi.x, hi.y, hi.z, hi.w);
   }
 }
 
-__device__ inline PageSources distinct_sources(int nv, const int *spage) {
-  PageSources ps{};
-  ps.nv = nv;
-  for (int j = 0; j < nv; ++j)
-    if (j == 0 || spage[j] != spage[j - 1]) {
-      const int id = spage[j];
-      if (ps.nu == 0) ps.u0 = id;
-      else if (ps.nu == 1) ps.u1 = id;
-      else if (ps.nu == 2) ps.u2 = id;
-      else if (ps.nu == 3) ps.u3 = id;
-      ++ps.nu;
-    }
-  return ps;
+// Rows [row0, min(row0 + kGatherRows, nl * hkv)) of a run: old pages page_a
+// (slots from slot0 on) and page_b (read only when slot0 > 0) -> dst.  With
+// SYNC every load of the workgroup lands before its first store, since dst
+// may be one of the sources.
+template <int D, class E, bool SYNC>
+__device__ inline void move_run(const Pools &p, int row0, int page_a, int page_b, int slot0, int dst) {
+  constexpr int VU = kPageUnits<D, E>;
+  constexpr int U = VU / P;                 // units per K row
+  constexpr int EPU = 16 / (int)sizeof(E);  // V^T elements per unit
+  constexpr int UPC = P / EPU;              // units per channel's row
+  const int un = threadIdx.x % VU, row = row0 + threadIdx.x / VU;
+  const bool in = row < p.nl * p.hkv;
+  const int sk = un + slot0 * U;
+  const int x = un % UPC * EPU + slot0;     // first element of the V^T unit, from page_a's row on
+  const int u0 = x / EPU, u1 = u0 + 1, sh = slot0 % EPU * (int)sizeof(E);
+  auto unit = [&](uint16_t *pool, int page, int u) {
+    return reinterpret_cast<uint4 *>(reinterpret_cast<E *>(pool) + row * p.head_stride +
+                                     (int64_t)page * p.page_stride) + u;
+  };
+  auto v_unit = [&](int u) { return *unit(p.v, u < UPC ? page_a : page_b, un / UPC * UPC + u % UPC); };
+  uint4 k{}, v0{}, v1{};
+  if (in) {
+    k = *unit(p.k, sk < VU ? page_a : page_b, sk % VU);
+    v0 = v_unit(u0);
+    if (sh != 0) v1 = v_unit(u1);
+  }
+  if constexpr (SYNC) {
+    __asm__ volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+  }
+  if (in) {
+    store_nt(unit(p.k, dst, un), k);
+    store_nt(unit(p.v, dst, un), funnel16(v0, v1, sh));
+  }
 }
 
-// Staged source page of slot j: the page changes among slots 1..j.
-__device__ inline int staged_of(int j, const int *spage) {
-  int f = 0;
-  for (int i = 1; i <= j; ++i) f += spage[i] != spage[i - 1];
-  return f;
-}
-
-// The destination page's V^T units from the staged source pages (or, with
-// more than kMaxStaged of them, element by element from the pools).
-template <int D, class E>
-__device__ inline void assemble_v(const Pools &p, int layer, int head, E *vd, const PageSources &ps,
-                                  const uint4 (*vbuf)[D * P * sizeof(E) / 16], const int *spage,
-                                  const int *sslot) {
-  constexpr int VU = D * P * (int)sizeof(E) / 16;
-  constexpr int EPU = 16 / (int)sizeof(E);
-  for (int idx = threadIdx.x; idx < VU; idx += blockDim.x) {
-    const int d = idx / (P / EPU), c = idx % (P / EPU);
+// Any other page (spans end or begin inside it, or it is the last and not
+// full): the same rows and units, each slot from its own old page, the
+// elements of a V^T unit one by one (they share their source's lines).
+// spage and sslot (LDS) hold the page id and slot of each of the nv sources.
+template <int D, class E, bool SYNC>
+__device__ inline void move_mixed(const Pools &p, int row0, int nv, const int *spage, const int *sslot,
+                                  int dst) {
+  constexpr int VU = kPageUnits<D, E>;
+  constexpr int U = VU / P;                // units per K row
+  constexpr int EPU = 16 / (int)sizeof(E); // V^T elements per unit
+  constexpr int UPC = P / EPU;             // units per channel's row
+  const int un = threadIdx.x % VU, row = row0 + threadIdx.x / VU;
+  const bool in = row < p.nl * p.hkv;
+  const int j = un / U, d = un / UPC, c = un % UPC;
+  auto chunk = [&](uint16_t *pool, int page) {
+    return reinterpret_cast<E *>(pool) + row * p.head_stride + (int64_t)page * p.page_stride;
+  };
+  uint4 k{}, v{};
+  if (in) {
+    if (j < nv) k = reinterpret_cast<const uint4 *>(chunk(p.k, spage[j]) + sslot[j] * D)[un % U];
     E out[EPU];
-    int f = staged_of(c * EPU, spage);
 #pragma unroll
     for (int e = 0; e < EPU; ++e) {
-      const int j = c * EPU + e;
-      if (e > 0 && j < ps.nv) f += spage[j] != spage[j - 1];
-      if (j >= ps.nv) out[e] = (E)0;
-      else if (ps.nu <= kMaxStaged) out[e] = reinterpret_cast<const E *>(vbuf[f])[d * P + sslot[j]];
-      else out[e] = chunk_of<E>(p.v, p, layer, spage[j], head)[d * P + sslot[j]];
+      const int jv = c * EPU + e;
+      out[e] = jv < nv ? chunk(p.v, spage[jv])[d * P + sslot[jv]] : (E)0;
     }
-    uint4 o;
-    __builtin_memcpy(&o, out, 16);
-    *reinterpret_cast<uint4 *>(vd + d * P + c * EPU) = o;
+    __builtin_memcpy(&v, out, 16);
   }
+  if constexpr (SYNC) {
+    __asm__ volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+  }
+  if (in) {
+    if (j < nv) store_nt(reinterpret_cast<uint4 *>(chunk(p.k, dst)) + un, k);
+    store_nt(reinterpret_cast<uint4 *>(chunk(p.v, dst)) + un, v);
+  }
+}
+
+// One destination page, tokens [t0, t0 + nv) of the compacted sequence, rows
+// from row0 on, and (with row 0) its positions: src_of gives a token's old
+// index (s0 and s1 the first and last, which are P - 1 apart in a whole page
+// exactly if it is a run), pt_row the old pages.
+template <int D, class E, bool SYNC, class SRC>
+__device__ inline void move_page(const Pools &p, int row0, int t0, int nv, int s0, int s1,
+                                 const SRC &src_of, const int32_t *pt_row, int dst, int *spage,
+                                 int *sslot) {
+  const int t = threadIdx.x;
+  const bool run = nv == P && s1 - s0 == P - 1;
+  const bool with_pos = row0 == 0 && t < nv;
+  int32_t pos = 0;
+  if (run) {
+    const int page_a = pt_row[s0 / P], page_b = pt_row[s1 / P]; // the same page when s0 % P = 0
+    if (with_pos) pos = p.pos[(int64_t)(s0 % P + t < P ? page_a : page_b) * P + (s0 + t) % P];
+    move_run<D, E, SYNC>(p, row0, page_a, page_b, s0 % P, dst);
+  } else {
+    if (t < nv) {
+      const int src = src_of(t0 + t);
+      spage[t] = pt_row[src / P];
+      sslot[t] = src % P;
+    }
+    __syncthreads();
+    if (with_pos) pos = p.pos[(int64_t)spage[t] * P + sslot[t]];
+    move_mixed<D, E, SYNC>(p, row0, nv, spage, sslot, dst);
+    if constexpr (SYNC) __syncthreads(); // the next page reuses the LDS
+  }
+  if (with_pos) p.pos[(int64_t)dst * P + t] = pos;
 }
 
 // ---------------------------------------------------------------------------
-// Gather: a workgroup per (fresh page pi0 + b, layer * Hkv + head) fills
+// Gather: a workgroup per (fresh page pi0 + b, kGatherRows rows) fills
 // destination page fp + pi0 + b with the kept tokens (fp + pi0 + b) * P + j,
-// j < P, j below L'.  K rows move as 16-byte units; V^T rows are assembled
-// in LDS from the (at most four, usually one or two) source pages staged
-// whole with 16-byte loads, then written as 16-byte units (more source pages
-// fall back to element moves).  Kept token t comes from old token
-// source_of(t) of the old pages, whose ids the page-table row still holds
-// (the new ids are written there after the last gather).  When the spans
-// travel in the kernel arguments, the first launch of an eviction also
-// writes the eviction index (keep, dst, src_of) in its first index_blocks
-// workgroups, alongside the copies, and takes the sources from the span
-// list so that it does not wait for the index; later launches of a chunked
-// eviction, and every launch after a separate index kernel, read src_of.  A fresh page is never a page
-// this or a later gather reads: it is either a page nothing held or an old
-// page whose tokens earlier gathers have all moved, so nothing is read after
-// being written.
+// j < P, j below L'.  Kept token t comes from old token source_of(t) of the
+// old pages, whose ids the page-table row still holds (the new ids are
+// written there after the last gather).  When the spans travel in the kernel
+// arguments, the first launch of an eviction also writes the eviction index
+// (keep, dst, src_of) in its first index_blocks workgroups, alongside the
+// copies, and takes the sources from the span list so that it does not wait
+// for the index; later launches of a chunked eviction, and every launch after
+// a separate index kernel, read src_of.  A fresh page is never a page this or
+// a later gather reads: it is either a page nothing held or an old page whose
+// tokens earlier gathers have all moved, so nothing is read after being
+// written.
 template <int D, class E>
 __global__ __launch_bounds__(256) void k_evict_gather(Pools p, GatherArgs a) {
-  constexpr int U = D * (int)sizeof(E) / 16;      // 16-byte units per K row
-  constexpr int VU = D * P * (int)sizeof(E) / 16; // 16-byte units of one page's V^T
-  constexpr int EPU = 16 / (int)sizeof(E);        // V^T elements per unit
-  constexpr int kMaxSrc = 4;                       // source pages staged in LDS
-  __shared__ int spage[P];
-  __shared__ int sslot[P];
-  __shared__ int sidx[P];  // the source's page index in the old list
-  __shared__ int nvalid;
-  __shared__ int upage[P]; // the distinct source pages, in order
-  __shared__ int uidx[P];  // slot j's source page in upage
-  __shared__ int n_up;
-  __shared__ uint4 vbuf[kMaxSrc][VU];
+  __shared__ int spage[P], sslot[P];
   __shared__ int32_t lsp[3 * kInlineSpans];
   const int n = a.n_new;
   const int lin = blockIdx.x + blockIdx.y * gridDim.x;
@@ -494,90 +545,27 @@ __global__ __launch_bounds__(256) void k_evict_gather(Pools p, GatherArgs a) {
     evict_index_block(a.ev, spans, lin);
     return;
   }
-  // Work item w = (KV row lh, tail page pl), page fastest.  Workgroups are
+  // Work item w = (group of rows, tail page pl), page fastest.  Workgroups are
   // dealt to the 8 XCDs in turn, so each XCD takes a contiguous range of
   // w: neighbouring destination pages, which share source pages, then hit
   // the same L2.  (Workgroups past the last item, which round the grid up
   // to whole rows, have nothing to do.)
-  const int total = n * p.nl * p.hkv;
+  const int groups = (p.nl * p.hkv + kGatherRows<D, E> - 1) / kGatherRows<D, E>;
+  const int total = n * groups;
   const int gl = lin - a.index_blocks;
   if (gl >= total) return;
   const int x = gl % 8, q = total / 8, r = total % 8;
   const int w = x * q + min(x, r) + gl / 8;
   const int pl = w % n;
-  const int lh = w / n;
-  const int pi = a.pi0 + pl;
-  const int layer = lh / p.hkv;
-  const int head = lh % p.hkv;
-  const int t0 = (a.fp + pi) * P;
+  const int row0 = w / n * kGatherRows<D, E>;
+  const int t0 = (a.fp + a.pi0 + pl) * P;
+  const int nv = min(P, a.new_len - t0);
   const int ns = a.ev.n_spans;
   auto src_of = [&](int t) { return from_spans ? source_of(spans, ns, t) : a.ev.src_of[t]; };
-  if (a.remap && t0 + P <= a.new_len) {
-    const int s0 = src_of(t0);
-    if (s0 % P == 0 && src_of(t0 + P - 1) == s0 + P - 1) return; // remapped, not copied
-  }
-  const int dst_page = new_page_id(a.ids, pl);
-  if (threadIdx.x < P) {
-    const int t = t0 + threadIdx.x;
-    if (t < a.new_len) {
-      const int src = src_of(t);
-      spage[threadIdx.x] = a.pt_row[src / P];
-      sslot[threadIdx.x] = src % P;
-      sidx[threadIdx.x] = src / P;
-    }
-  }
-  if (threadIdx.x == 0) nvalid = min(P, a.new_len - t0);
-  __syncthreads();
-  const int nv = nvalid;
-  if ((int)threadIdx.x < nv) {
-    // sources are in increasing old order, so slot j's source page is the
-    // number of page changes among slots 1..j
-    int f = 0;
-    for (int i = 1; i <= (int)threadIdx.x; ++i) f += sidx[i] != sidx[i - 1];
-    uidx[threadIdx.x] = f;
-    upage[f] = spage[threadIdx.x];
-    if ((int)threadIdx.x == nv - 1) n_up = f + 1;
-  }
-
-  E *kd = chunk_of<E>(p.k, p, layer, dst_page, head);
-  for (int idx = threadIdx.x; idx < nv * U; idx += blockDim.x) {
-    const int j = idx / U, u = idx % U;
-    const uint4 *ks = reinterpret_cast<const uint4 *>(chunk_of<E>(p.k, p, layer, spage[j], head) +
-                                                      sslot[j] * D);
-    *(reinterpret_cast<uint4 *>(kd + j * D) + u) = ks[u];
-  }
-  __syncthreads();
-  const int nu = n_up;
-  E *vd = chunk_of<E>(p.v, p, layer, dst_page, head);
-  if (nu <= kMaxSrc) {
-    // stage the source pages' V^T (16-byte loads), then assemble each
-    // destination unit of EPU slots of one channel from LDS
-    for (int u = 0; u < nu; ++u) {
-      const uint4 *vs = reinterpret_cast<const uint4 *>(chunk_of<E>(p.v, p, layer, upage[u], head));
-      for (int idx = threadIdx.x; idx < VU; idx += blockDim.x) vbuf[u][idx] = vs[idx];
-    }
-    __syncthreads();
-    for (int idx = threadIdx.x; idx < VU; idx += blockDim.x) {
-      const int d = idx / (P / EPU), c = idx % (P / EPU);
-      E out[EPU];
-#pragma unroll
-      for (int e = 0; e < EPU; ++e) {
-        const int j = c * EPU + e;
-        out[e] = j < nv ? reinterpret_cast<const E *>(vbuf[uidx[j]])[d * P + sslot[j]] : (E)0;
-      }
-      uint4 o;
-      __builtin_memcpy(&o, out, 16);
-      *reinterpret_cast<uint4 *>(vd + d * P + c * EPU) = o;
-    }
-  } else {
-    for (int idx = threadIdx.x; idx < D * P; idx += blockDim.x) {
-      const int j = idx % P, d = idx / P;
-      if (j < nv) vd[d * P + j] = chunk_of<E>(p.v, p, layer, spage[j], head)[d * P + sslot[j]];
-    }
-  }
-  if (lh == 0 && threadIdx.x < nv)
-    p.pos[(int64_t)dst_page * P + threadIdx.x] =
-        p.pos[(int64_t)spage[threadIdx.x] * P + sslot[threadIdx.x]];
+  const int s0 = __builtin_amdgcn_readfirstlane(src_of(t0));
+  const int s1 = __builtin_amdgcn_readfirstlane(src_of(t0 + nv - 1));
+  if (a.remap && nv == P && s0 % P == 0 && s1 - s0 == P - 1) return; // remapped, not copied
+  move_page<D, E, false>(p, row0, t0, nv, s0, s1, src_of, a.pt_row, new_page_id(a.ids, pl), spage, sslot);
 }
 
 // ---------------------------------------------------------------------------
@@ -586,29 +574,21 @@ __global__ __launch_bounds__(256) void k_evict_gather(Pools p, GatherArgs a) {
 // tokens come from old list indices >= fp + k, so a page is never read after
 // a page before it in the tail has been rewritten, as long as the pages of
 // one launch read no page of the launch but their own: the host cuts the
-// tail into such runs (round mode, one workgroup per page and layer * Hkv +
-// head, like the gather), or hands a run of short ones to sweep mode, where
-// one workgroup per layer * Hkv + head takes the pages in order.  Either way
-// a workgroup loads everything a page needs (K rows, the V^T of its source
-// pages, positions) in one round into LDS, waits at a barrier until every
-// load of the page has landed there, and only then writes the page, which
-// may be one of its own sources.
+// tail into such runs (round mode, a workgroup per page and kGatherRows rows,
+// like the gather), or hands a run of short ones to sweep mode, where one
+// workgroup per kGatherRows rows takes the pages in order.  Either way a
+// workgroup has loaded everything a page of its rows needs before it writes
+// the page, which may be one of its own sources.
 template <int D, class E>
 __global__ __launch_bounds__(256) void k_evict_inplace(Pools p, InplaceArgs a) {
-  constexpr int U = D * (int)sizeof(E) / 16;      // 16-byte units per K row
-  constexpr int VU = D * P * (int)sizeof(E) / 16; // 16-byte units of one page's V^T
-  __shared__ int spage[P];
-  __shared__ int sslot[P];
-  __shared__ uint4 kbuf[P * U];
-  __shared__ uint4 vbuf[kMaxStaged][VU];
-  __shared__ int32_t pbuf[P];
-  int pl0, pl1, lh;
+  __shared__ int spage[P], sslot[P];
+  int pl0, pl1, row0;
   if (a.sweep) {
     pl0 = 0;
     pl1 = a.n_pages;
-    lh = blockIdx.x;
+    row0 = blockIdx.x * kGatherRows<D, E>;
   } else {
-    // consecutive pages of one KV row to one XCD, as in the gather
+    // consecutive pages of one group of rows to one XCD, as in the gather
     const int n = gridDim.x;
     const int total = n * gridDim.y;
     const int lin = blockIdx.x + blockIdx.y * n;
@@ -616,55 +596,16 @@ __global__ __launch_bounds__(256) void k_evict_inplace(Pools p, InplaceArgs a) {
     const int w = x * q + min(x, r) + lin / 8;
     pl0 = w % n;
     pl1 = pl0 + 1;
-    lh = w / n;
+    row0 = w / n * kGatherRows<D, E>;
   }
-  const int layer = lh / p.hkv;
-  const int head = lh % p.hkv;
+  auto src_of = [&](int t) { return a.src_of[t]; };
   for (int pl = pl0; pl < pl1; ++pl) {
     const int k = a.k0 + pl;
     const int t0 = (a.fp + k) * P;
-    const int dst_page = new_page_id(a.ids, k);
     const int nv = min(P, a.new_len - t0);
-    load_sources(a.src_of, a.pt_row, t0, nv, spage, sslot);
-    __syncthreads();
-    const PageSources ps = distinct_sources(nv, spage);
-    // ---- read: everything the page needs, into LDS, in one round ----
-    for (int idx = threadIdx.x; idx < nv * U; idx += blockDim.x) {
-      const int j = idx / U, u = idx % U;
-      kbuf[idx] = reinterpret_cast<const uint4 *>(chunk_of<E>(p.k, p, layer, spage[j], head) +
-                                                  sslot[j] * D)[u];
-    }
-    if (ps.nu <= kMaxStaged) {
-#pragma unroll
-      for (int u = 0; u < kMaxStaged; ++u) {
-        if (u >= ps.nu) break;
-        const uint4 *vs = reinterpret_cast<const uint4 *>(chunk_of<E>(p.v, p, layer, ps.up(u), head));
-        for (int idx = threadIdx.x; idx < VU; idx += blockDim.x) vbuf[u][idx] = vs[idx];
-      }
-    } else {
-      E *vo = reinterpret_cast<E *>(&vbuf[0][0]);
-      for (int idx = threadIdx.x; idx < D * P; idx += blockDim.x) {
-        const int j = idx % P, d = idx / P;
-        vo[idx] = j < nv ? chunk_of<E>(p.v, p, layer, spage[j], head)[d * P + sslot[j]] : (E)0;
-      }
-    }
-    if (lh == 0 && (int)threadIdx.x < nv)
-      pbuf[threadIdx.x] = p.pos[(int64_t)spage[threadIdx.x] * P + sslot[threadIdx.x]];
-    // every load of this page's sources has been written to LDS by now: the
-    // page itself may be overwritten
-    __syncthreads();
-    // ---- write ----
-    uint4 *kd = reinterpret_cast<uint4 *>(chunk_of<E>(p.k, p, layer, dst_page, head));
-    for (int idx = threadIdx.x; idx < nv * U; idx += blockDim.x) kd[idx] = kbuf[idx];
-    E *vd = chunk_of<E>(p.v, p, layer, dst_page, head);
-    if (ps.nu <= kMaxStaged) {
-      assemble_v<D, E>(p, layer, head, vd, ps, vbuf, spage, sslot);
-    } else {
-      for (int idx = threadIdx.x; idx < VU; idx += blockDim.x)
-        reinterpret_cast<uint4 *>(vd)[idx] = vbuf[0][idx];
-    }
-    if (lh == 0 && (int)threadIdx.x < nv) p.pos[(int64_t)dst_page * P + threadIdx.x] = pbuf[threadIdx.x];
-    __syncthreads(); // the next page reuses the LDS
+    const int s0 = __builtin_amdgcn_readfirstlane(src_of(t0));
+    const int s1 = __builtin_amdgcn_readfirstlane(src_of(t0 + nv - 1));
+    move_page<D, E, true>(p, row0, t0, nv, s0, s1, src_of, a.pt_row, new_page_id(a.ids, k), spage, sslot);
   }
 }
 
@@ -764,9 +705,18 @@ hipError_t launch_write_ids(int32_t *dst, const NewIds &ids, int32_t n, hipStrea
   return hipGetLastError();
 }
 
+// Groups of rows that a workgroup of the gather takes.
+static int gather_groups(const Pools &p) {
+  const int rows = p.nl * p.hkv;
+  const int per = p.kv8 ? (p.d == 128 ? kGatherRows<128, uint8_t> : kGatherRows<64, uint8_t>)
+                        : (p.d == 128 ? kGatherRows<128, uint16_t> : kGatherRows<64, uint16_t>);
+  return (rows + per - 1) / per;
+}
+
 hipError_t launch_evict_inplace(const Pools &p, const InplaceArgs &a, hipStream_t s) {
   if (a.n_pages <= 0) return hipSuccess;
-  const dim3 grid = a.sweep ? dim3(p.nl * p.hkv) : dim3(a.n_pages, p.nl * p.hkv);
+  const int groups = gather_groups(p);
+  const dim3 grid = a.sweep ? dim3(groups) : dim3(a.n_pages, groups);
   if (p.kv8) {
     if (p.d == 128)
       hipLaunchKernelGGL((k_evict_inplace<128, uint8_t>), grid, dim3(256), 0, s, p, a);
@@ -781,9 +731,9 @@ hipError_t launch_evict_inplace(const Pools &p, const InplaceArgs &a, hipStream_
 
 hipError_t launch_evict_gather(const Pools &p, const GatherArgs &a, hipStream_t s) {
   if (a.n_new == 0) return hipSuccess;
-  // rows of n_new workgroups: the copies' (layer, head) rows, then enough
-  // for the index blocks
-  const int rows = p.nl * p.hkv + (a.index_blocks + a.n_new - 1) / a.n_new;
+  // rows of n_new workgroups: the copies' groups of (layer, head) rows, then
+  // enough for the index blocks
+  const int rows = gather_groups(p) + (a.index_blocks + a.n_new - 1) / a.n_new;
   dim3 grid(a.n_new, rows);
   if (p.kv8) {
     if (p.d == 128)

@@ -1760,13 +1760,15 @@ sq_status sq_evict_spans_ex(sq_store *s, sq_seq h, const int32_t *cursor_ids, in
     // token's source from the spans in its kernel arguments, and the index
     // (keep, dst, src_of: for later gather launches, the in-place kernel and
     // the debug read) runs as extra workgroups of that launch, which saves
-    // the index kernel and the gap after it (8-9 us).  Searching the spans
-    // lengthens each gather workgroup, though: on the 64K compaction (11K
-    // workgroups) the launch took 39.5 us against 33 us for the gather
-    // alone, a cost that grows with the launch.  So a launch of more than
-    // kFuseIndexMaxWgs workgroups keeps the index kernel, as do the
-    // in-place kernel, an eviction that copies no page, and spans too many
-    // to travel in the arguments; the gathers then read src_of.
+    // the index kernel and the gap after it (3-7 us: 32 against 28 us for
+    // 9000 tokens of 4 layers, 38 against 34 for the 64K compaction of one
+    // layer).  Searching the spans lengthens each gather workgroup, though, a
+    // cost that grows with the launch: 30K tokens of 4 layers (36K pages and
+    // rows) took 105 us so against 97, 60K of an 8-bit store 112 against 97.
+    // So a launch of more than kFuseIndexMaxWgs (page, row) pairs keeps the
+    // index kernel, as do the in-place kernel, an eviction that copies no
+    // page, and spans too many to travel in the arguments; the gathers then
+    // read src_of.
     constexpr int64_t kFuseIndexMaxWgs = 12288;
     int64_t first_wgs = 0;
     if (!inplace)

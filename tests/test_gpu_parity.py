@@ -326,3 +326,45 @@ def test_append_batch_matches_appends(sq):
     t.check_state()
     errs, _ = t.decode_errors(seqs, layer=1)
     assert max(errs.values()) <= TOL
+
+
+@pytest.mark.parametrize("kw", [{}, {"evict_inplace": True}, {"evict_chunk_pages": 3}, {"evict_remap": True}])
+@pytest.mark.parametrize("nl,hkv,d,kv8", [(1, 1, 128, False), (3, 1, 64, False), (1, 3, 128, True), (1, 5, 64, True),
+                                          (2, 2, 128, False)])
+def test_evicted_pages_at_every_shift(sq, nl, hkv, d, kv8, kw):
+    """A tail moved by every number of slots in turn (runs across two pages at
+    each shift, aligned ones among them), pages made of up to eight sources and
+    a last page that is not full, with row counts that do not fill a
+    workgroup: each kept token's K, V and position bit for bit."""
+    import torch
+    rng = np.random.default_rng(41 * d + nl)
+    L, n = 1200, 16
+    s = sq.Store(nl, hkv, hkv, d, 200, 4, 200, device="cuda", kv_scales=[[0.02, 0.03]] * nl if kv8 else None, **kw)
+
+    def held(h):
+        pt = torch.tensor(s.page_table(h), device="cuda")
+        tok = torch.arange(s.seq_info(h)["length"], device="cuda")
+        pg, sl = pt[tok // 16], tok % 16
+        k = s.k_pool.view(torch.uint8 if kv8 else torch.int16)[:, :, pg, sl]
+        v = s.v_pool.view(torch.uint8 if kv8 else torch.int16).transpose(3, 4)[:, :, pg, sl]
+        return k.clone(), v.clone(), s.pos_pool[pg, sl].clone()
+
+    for shift in range(1, 17):
+        a = s.seq_create()
+        k, v = (wl.to_torch_bf16(wl.normal_bf16(rng, (nl, L, hkv, d)), "cuda") for _ in range(2))
+        s.append(a, k, v)
+        before = held(a)
+        # one span of `shift` tokens, a stretch of single tokens, another span
+        spans = [(37, 37 + shift)] + [(600 + 4 * i, 602 + 4 * i) for i in range(n)] + [(900, 900 + 2 * shift)]
+        keep = np.ones(L, dtype=bool)
+        for i, (x, y) in enumerate(spans):
+            s.span_mark(a, i, x, y)
+            keep[x:y] = False
+        s.evict(a, list(range(len(spans))))
+        at = torch.from_numpy(np.flatnonzero(keep)).to("cuda")
+        torch.cuda.synchronize()
+        for x, y in zip(before, held(a)):
+            x = x[at] if x.ndim == 1 else x[:, :, at]
+            assert torch.equal(x, y), shift
+        s.release(a)
+    s.close()
