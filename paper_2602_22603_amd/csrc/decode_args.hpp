@@ -5,6 +5,8 @@
 
 #include "sq_common.hpp"
 
+#include <cstddef>
+
 namespace sq {
 
 // ---- decode ---------------------------------------------------------------
@@ -156,15 +158,26 @@ struct StepAppend {
 // The step plan, in device memory: written once per step, read by every
 // layer's launches, whose arguments therefore stay the same from step to
 // step.
+// Up to kStepRows (entry, KV head) pairs also bring their merge row lists
+// (n_rows != 0), at index b * Hkv + g, so that a merge workgroup has all it
+// needs after one round of loads; without them it derives its own from the
+// tables, one dependent round after another (step of 22.7K tokens, 32/8 heads
+// of 128: 6.6 us a merge, 5.5 with the lists).  The upload is cut after
+// the last part the step uses.
+constexpr int kStepRows = 128;
 struct StepPlan {
   DecodeDyn dec[2];   // VALU, MFMA launch over every old token
   MergeDyn merge;
-  DecodeDyn dec_w[2]; // the same over the window's old tokens (a windowed step)
-  MergeDyn merge_w;
   StepAppend app;
   int32_t batch;      // entries of the step; merge workgroups past it do nothing
-  int32_t pad;
+  int32_t n_rows;     // entries of rows (and rows_w), or 0
+  MergeRows rows[kStepRows];
+  DecodeDyn dec_w[2]; // the same over the window's old tokens (a windowed step)
+  MergeDyn merge_w;
+  int32_t pad[2];
+  MergeRows rows_w[kStepRows];
 };
+static_assert(sizeof(StepPlan) % 16 == 0 && offsetof(StepPlan, rows) % 16 == 0, "uploaded as 16-byte units");
 
 struct StepMergeArgs {
   MergeStatic st;

@@ -1043,6 +1043,22 @@ __device__ inline void merge_body(const MergeStatic &a, const MP &mp, const SA &
   int cum[kMaxSrc + 1];
   int32_t base[kMaxSrc], step[kMaxSrc];
   cum[0] = 0;
+  // a step's new token, read now so that it arrives with the partials
+  uint16_t kraw = 0, vraw = 0, qraw = 0;
+  int app_page = 0, app_slot = 0, app_pos = 0;
+  if constexpr (APPEND) {
+    if (sh == NSH - 1) {
+      const int64_t kv = ((int64_t)b * a.hkv + g) * D + c;
+      kraw = sa.k_new[kv];
+      vraw = sa.v_new[kv];
+      qraw = sa.q[((int64_t)b * a.hq + h) * D + c];
+    }
+    const SQ_CONST StepAppend &ap = ((const SQ_CONST StepPlan *)sa.plan)->app;
+    app_page = ap.page[b];
+    app_slot = ap.slot[b];
+    app_pos = ap.pos[b];
+    __asm__ volatile("" ::"s"(app_page), "s"(app_slot), "s"(app_pos));
+  }
   // (read before the test, so that they come in the first round of
   // argument reads whichever way it goes)
   int32_t ib[kMaxSrc], ics[kMaxSrc];
@@ -1146,8 +1162,6 @@ __device__ inline void merge_body(const MergeStatic &a, const MP &mp, const SA &
     s_a[NSH][c] = 0.f;
     float vnew = 0.f;
     if constexpr (APPEND) {
-      const int64_t kv = (int64_t)b * a.hkv + g;
-      const uint16_t kraw = sa.k_new[kv * D + c], vraw = sa.v_new[kv * D + c];
       float kf = __uint_as_float((uint32_t)kraw << 16), vf = __uint_as_float((uint32_t)vraw << 16);
       uint16_t kb = kraw, vb = vraw;
       if constexpr (KV8) { // the codes, and their values as the store holds them
@@ -1156,14 +1170,13 @@ __device__ inline void merge_body(const MergeStatic &a, const MP &mp, const SA &
         kf = __uint_as_float(e4m3x4_to_bf16(kb).x << 16);
         vf = __uint_as_float(e4m3x4_to_bf16(vb).x << 16);
       }
-      float dot = __uint_as_float((uint32_t)sa.q[((int64_t)b * a.hq + h) * D + c] << 16) * kf;
+      float dot = __uint_as_float((uint32_t)qraw << 16) * kf;
 #pragma unroll
       for (int o = 32; o > 0; o >>= 1) dot += __shfl_xor(dot, o);
       if ((tid & 63) == 0) s_dot[(tid >> 6) % (D / 64)] = dot;
       vnew = vf;
       if (hr == 0) { // store the new token of KV head g (the same in every head's workgroup)
-        const SQ_CONST StepAppend &ap = ((const SQ_CONST StepPlan *)sa.plan)->app;
-        const int page = ap.page[b], slot = ap.slot[b];
+        const int page = app_page, slot = app_slot;
         const int64_t pb = (int64_t)g * sa.head_stride + (int64_t)page * sa.page_stride;
         if constexpr (KV8) {
           uint8_t *k8 = reinterpret_cast<uint8_t *>(sa.k), *v8 = reinterpret_cast<uint8_t *>(sa.v);
@@ -1173,7 +1186,7 @@ __device__ inline void merge_body(const MergeStatic &a, const MP &mp, const SA &
           sa.k[pb + (int64_t)slot * D + c] = kb;
           sa.v[pb + (int64_t)c * P + slot] = vb;
         }
-        if (c == 0 && g == 0) sa.pos[(int64_t)page * P + slot] = ap.pos[b];
+        if (c == 0 && g == 0) sa.pos[(int64_t)page * P + slot] = app_pos;
       }
     }
     s_a[NSH + 1][c] = vnew;
@@ -1213,25 +1226,29 @@ __device__ inline void merge_body(const MergeStatic &a, const MP &mp, const SA &
   }
 }
 
-__constant__ MergeRows kNoRows = {}; // step merges derive their row lists from the plan
-
 template <int D>
 __global__ __launch_bounds__(64 * kMergeWaves) void k_decode_merge(MergeArgs a) {
   // (from the workgroup's own ids: no argument read before this one)
   const int bg = min((int)(blockIdx.z * kInlineG + blockIdx.y), kInlineRows - 1);
   merge_body<D, false>(a.st, ArgMerge{a.dyn}, 0, a.n_inline != 0, a.rows[bg]);
 }
-template <int D>
+template <int D, bool KV8>
 __global__ __launch_bounds__(64 * kMergeWaves) void k_step_merge(StepMergeArgs a) {
   const SQ_CONST StepPlan *plan = (const SQ_CONST StepPlan *)a.plan;
-  if ((int)blockIdx.z >= plan->batch) return; // a replay sized for a larger batch
-  merge_body<D, true>(a.st, DevMerge{a.windowed ? &plan->merge_w : &plan->merge}, a, false, kNoRows);
-}
-template <int D> __global__ __launch_bounds__(64 * kMergeWaves) void k_step_merge8(StepMergeArgs a) {
-  const SQ_CONST StepPlan *plan = (const SQ_CONST StepPlan *)a.plan;
-  if ((int)blockIdx.z >= plan->batch) return;
-  merge_body<D, true, DevMerge, StepMergeArgs, true>(
-      a.st, DevMerge{a.windowed ? &plan->merge_w : &plan->merge}, a, false, kNoRows);
+  // this (entry, KV head)'s row list, if the plan has it (in bounds always)
+  const int i = min((int)(blockIdx.z * a.st.hkv + blockIdx.y), kStepRows - 1);
+  const SQ_CONST MergeRows *src = a.windowed ? &plan->rows_w[i] : &plan->rows[i];
+  const int n_rows = plan->n_rows, batch = plan->batch;
+  MergeRows rows;
+#pragma unroll
+  for (int e = 0; e < kMaxSrc; ++e) {
+    rows.base[e] = src->base[e];
+    rows.cnt_step[e] = src->cnt_step[e];
+    __asm__ volatile("" ::"s"(rows.base[e]), "s"(rows.cnt_step[e]));
+  }
+  if ((int)blockIdx.z >= batch) return; // a replay sized for a larger batch
+  merge_body<D, true, DevMerge, StepMergeArgs, KV8>(
+      a.st, DevMerge{a.windowed ? &plan->merge_w : &plan->merge}, a, n_rows != 0, rows);
 }
 
 template <int D, bool NT, bool KV8>
@@ -1454,13 +1471,13 @@ hipError_t launch_step_merge(int d, int batch, const StepMergeArgs &a, bool kv8,
   const dim3 grid(a.st.group, a.st.hkv, batch), block(64 * kMergeWaves);
   if (kv8) {
     if (d == 128)
-      hipLaunchKernelGGL(k_step_merge8<128>, grid, block, 0, s, a);
+      hipLaunchKernelGGL((k_step_merge<128, true>), grid, block, 0, s, a);
     else
-      hipLaunchKernelGGL(k_step_merge8<64>, grid, block, 0, s, a);
+      hipLaunchKernelGGL((k_step_merge<64, true>), grid, block, 0, s, a);
   } else if (d == 128)
-    hipLaunchKernelGGL(k_step_merge<128>, grid, block, 0, s, a);
+    hipLaunchKernelGGL((k_step_merge<128, false>), grid, block, 0, s, a);
   else
-    hipLaunchKernelGGL(k_step_merge<64>, grid, block, 0, s, a);
+    hipLaunchKernelGGL((k_step_merge<64, false>), grid, block, 0, s, a);
   return hipGetLastError();
 }
 

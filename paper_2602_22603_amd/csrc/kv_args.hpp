@@ -118,10 +118,15 @@ hipError_t launch_append(const Pools &p, const AppendArgs &a, const void *k_new,
                          const void *v_new, hipStream_t s);
 hipError_t launch_append_batch(const Pools &p, const AppendBatchArgs &a, const void *k_new,
                                const void *v_new, hipStream_t s);
-hipError_t launch_set_entries(const SetEntries &a, hipStream_t s);
-hipError_t launch_copy_i32(int32_t *dst, const int32_t *src, int32_t n, int32_t tail_index,
-                           int32_t tail_value, hipStream_t s);
-hipError_t launch_copy_page(const Pools &p, int32_t src_page, int32_t dst_page, hipStream_t s);
+// dst[0 .. bytes) = src (pinned host memory; both 16-byte aligned, bytes a
+// multiple of 16), and the entries.
+hipError_t launch_step_upload(void *dst, const void *src, int64_t bytes, const SetEntries &a,
+                              hipStream_t s);
+// A fork: dst[i] = src[i] for i < n of the page-table rows, and, when
+// tail_page >= 0, dst[n] = tail_page and every layer's and head's page
+// src_tail copied to it.
+hipError_t launch_fork(const Pools &p, int32_t *dst, const int32_t *src, int32_t n, int32_t src_tail,
+                       int32_t tail_page, hipStream_t s);
 // dst[i] = value for i < n.
 hipError_t launch_fill_i32(int32_t *dst, int32_t value, int32_t n, hipStream_t s);
 hipError_t launch_evict_index(const EvictArgs &a, hipStream_t s);

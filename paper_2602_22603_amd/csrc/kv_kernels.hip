@@ -22,12 +22,6 @@ namespace {
 
 constexpr int P = kPage;
 
-__device__ inline const uint16_t *k_chunk(const Pools &p, int layer, int page, int head) {
-  return p.k + layer * p.layer_stride + (int64_t)page * p.page_stride + head * p.head_stride;
-}
-__device__ inline const uint16_t *v_chunk(const Pools &p, int layer, int page, int head) {
-  return p.v + layer * p.layer_stride + (int64_t)page * p.page_stride + head * p.head_stride;
-}
 __device__ inline uint16_t *k_chunk_w(const Pools &p, int layer, int page, int head) {
   return p.k + layer * p.layer_stride + (int64_t)page * p.page_stride + head * p.head_stride;
 }
@@ -245,16 +239,14 @@ __global__ __launch_bounds__(64) void k_append_batch8(Pools p, AppendBatchArgs a
   }
 }
 
-// dst[i] = src[i] for i < n, then dst[n] = tail_value when tail_value >= 0.
-__global__ __launch_bounds__(64) void k_set_entries(SetEntries a) {
-  if ((int)threadIdx.x < a.n) a.base[a.index[threadIdx.x]] = a.value[threadIdx.x];
-}
-
-__global__ __launch_bounds__(256) void k_copy_i32(int32_t *dst, const int32_t *src, int32_t n,
-                                                  int32_t tail_value) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) dst[i] = src[i];
-  if (i == n && tail_value >= 0) dst[n] = tail_value;
+// A step's plan from pinned host memory, and its new page-table entries.  (A
+// kernel, 3 us, and no hipMemcpyAsync: the copy engine's hand-over to the kernels
+// around it cost 10.)
+__global__ __launch_bounds__(256) void k_step_upload(uint4 *dst, const uint4 *src, int32_t n16,
+                                                     SetEntries a) {
+  const int i = blockIdx.x * 256 + threadIdx.x;
+  if (i < n16) dst[i] = src[i];
+  if (blockIdx.x == 0 && (int)threadIdx.x < a.n) a.base[a.index[threadIdx.x]] = a.value[threadIdx.x];
 }
 
 __global__ __launch_bounds__(256) void k_fill_i32(int32_t *dst, int32_t value, int32_t n) {
@@ -262,23 +254,31 @@ __global__ __launch_bounds__(256) void k_fill_i32(int32_t *dst, int32_t value, i
   if (i < n) dst[i] = value;
 }
 
-// Whole-page copy (every layer and head, K, V and pos): the fork's tail page.
+// Fork: the first pt_blocks workgroups copy the page-table row and set its
+// tail entry, the others (one per layer and head) copy the tail page.
 template <int D, class E>
-__global__ __launch_bounds__(256) void k_copy_page(Pools p, int32_t src_page, int32_t dst_page) {
+__global__ __launch_bounds__(256) void k_fork(Pools p, int32_t *dst, const int32_t *src, int32_t n,
+                                              int32_t src_tail, int32_t tail_page, int32_t pt_blocks) {
+  if ((int)blockIdx.x < pt_blocks) {
+    const int i = blockIdx.x * 256 + threadIdx.x;
+    if (i < n) dst[i] = src[i];
+    if (i == n && tail_page >= 0) dst[n] = tail_page;
+    return;
+  }
   constexpr int U = P * D * (int)sizeof(E) / 16;
-  const int lh = blockIdx.x;
+  const int lh = blockIdx.x - pt_blocks;
   const int layer = lh / p.hkv;
   const int head = lh % p.hkv;
-  const uint4 *ks = reinterpret_cast<const uint4 *>(chunk_of<E>(p.k, p, layer, src_page, head));
-  const uint4 *vs = reinterpret_cast<const uint4 *>(chunk_of<E>(p.v, p, layer, src_page, head));
-  uint4 *kd = reinterpret_cast<uint4 *>(chunk_of<E>(p.k, p, layer, dst_page, head));
-  uint4 *vd = reinterpret_cast<uint4 *>(chunk_of<E>(p.v, p, layer, dst_page, head));
+  const uint4 *ks = reinterpret_cast<const uint4 *>(chunk_of<E>(p.k, p, layer, src_tail, head));
+  const uint4 *vs = reinterpret_cast<const uint4 *>(chunk_of<E>(p.v, p, layer, src_tail, head));
+  uint4 *kd = reinterpret_cast<uint4 *>(chunk_of<E>(p.k, p, layer, tail_page, head));
+  uint4 *vd = reinterpret_cast<uint4 *>(chunk_of<E>(p.v, p, layer, tail_page, head));
   for (int u = threadIdx.x; u < U; u += blockDim.x) {
     kd[u] = ks[u];
     vd[u] = vs[u];
   }
   if (lh == 0 && threadIdx.x < P)
-    p.pos[(int64_t)dst_page * P + threadIdx.x] = p.pos[(int64_t)src_page * P + threadIdx.x];
+    p.pos[(int64_t)tail_page * P + threadIdx.x] = p.pos[(int64_t)src_tail * P + threadIdx.x];
 }
 
 // ---------------------------------------------------------------------------
@@ -662,33 +662,28 @@ hipError_t launch_fill_i32(int32_t *dst, int32_t value, int32_t n, hipStream_t s
   return hipGetLastError();
 }
 
-hipError_t launch_set_entries(const SetEntries &a, hipStream_t s) {
-  if (a.n <= 0) return hipSuccess;
-  if (a.n > kMaxBatch) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_set_entries, dim3(1), dim3(64), 0, s, a);
+hipError_t launch_step_upload(void *dst, const void *src, int64_t bytes, const SetEntries &a,
+                              hipStream_t s) {
+  if (a.n > kMaxBatch || bytes % 16 != 0) return hipErrorInvalidValue;
+  const int32_t n16 = (int32_t)(bytes / 16);
+  hipLaunchKernelGGL(k_step_upload, dim3((n16 + 255) / 256), dim3(256), 0, s, static_cast<uint4 *>(dst),
+                     static_cast<const uint4 *>(src), n16, a);
   return hipGetLastError();
 }
 
-hipError_t launch_copy_i32(int32_t *dst, const int32_t *src, int32_t n, int32_t tail_index,
-                           int32_t tail_value, hipStream_t s) {
-  (void)tail_index;
-  const int total = n + 1;
-  hipLaunchKernelGGL(k_copy_i32, dim3((total + 255) / 256), dim3(256), 0, s, dst, src, n,
-                     tail_value);
-  return hipGetLastError();
-}
-
-hipError_t launch_copy_page(const Pools &p, int32_t src_page, int32_t dst_page, hipStream_t s) {
-  const dim3 grid(p.nl * p.hkv), block(256);
+hipError_t launch_fork(const Pools &p, int32_t *dst, const int32_t *src, int32_t n, int32_t src_tail,
+                       int32_t tail_page, hipStream_t s) {
+  const int32_t ptb = (n + 1 + 255) / 256;
+  const dim3 grid(ptb + (tail_page >= 0 ? p.nl * p.hkv : 0)), block(256);
   if (p.kv8) {
     if (p.d == 128)
-      hipLaunchKernelGGL((k_copy_page<128, uint8_t>), grid, block, 0, s, p, src_page, dst_page);
+      hipLaunchKernelGGL((k_fork<128, uint8_t>), grid, block, 0, s, p, dst, src, n, src_tail, tail_page, ptb);
     else
-      hipLaunchKernelGGL((k_copy_page<64, uint8_t>), grid, block, 0, s, p, src_page, dst_page);
+      hipLaunchKernelGGL((k_fork<64, uint8_t>), grid, block, 0, s, p, dst, src, n, src_tail, tail_page, ptb);
   } else if (p.d == 128)
-    hipLaunchKernelGGL((k_copy_page<128, uint16_t>), grid, block, 0, s, p, src_page, dst_page);
+    hipLaunchKernelGGL((k_fork<128, uint16_t>), grid, block, 0, s, p, dst, src, n, src_tail, tail_page, ptb);
   else
-    hipLaunchKernelGGL((k_copy_page<64, uint16_t>), grid, block, 0, s, p, src_page, dst_page);
+    hipLaunchKernelGGL((k_fork<64, uint16_t>), grid, block, 0, s, p, dst, src, n, src_tail, tail_page, ptb);
   return hipGetLastError();
 }
 

@@ -894,16 +894,14 @@ ExtendPlan plan_extend(const sq_store *s, int64_t n, int64_t L, int64_t window) 
   return best;
 }
 
-// A small call's merge row lists in the arguments (MergeRows): the same
-// arithmetic the merge kernel does from the plan's tables, done here once.
-void fill_inline_rows(const sq_store *s, int batch, sq::MergeArgs *ma) {
-  const sq::MergeDyn &md = ma->dyn;
+// The merge row lists (MergeRows) of every (entry b, KV head g), at b * pitch
+// + g: the same arithmetic the merge kernel does from the plan's tables, done
+// here once.
+void fill_rows(const sq_store *s, int batch, int pitch, const sq::MergeDyn &md, sq::MergeRows *rows) {
   const int hkv = s->cfg.num_kv_heads;
-  ma->n_inline = 0;
-  if (hkv > sq::kInlineG || (int64_t)batch * sq::kInlineG > sq::kInlineRows) return;
   for (int b = 0; b < batch; ++b)
     for (int g = 0; g < hkv; ++g) {
-      sq::MergeRows &r = ma->rows[b * sq::kInlineG + g];
+      sq::MergeRows &r = rows[b * pitch + g];
       for (int e = 0; e < sq::kMaxSrc; ++e) {
         r.base[e] = 0;
         r.cnt_step[e] = 0;
@@ -920,6 +918,13 @@ void fill_inline_rows(const sq_store *s, int batch, sq::MergeArgs *ma) {
         r.cnt_step[e] = (w_hi - w_lo + 1) | (rb * sq::kRows) << 16;
       }
     }
+}
+
+// A small call's row lists travel in the arguments.
+void fill_inline_rows(const sq_store *s, int batch, sq::MergeArgs *ma) {
+  ma->n_inline = 0;
+  if (s->cfg.num_kv_heads > sq::kInlineG || (int64_t)batch * sq::kInlineG > sq::kInlineRows) return;
+  fill_rows(s, batch, sq::kInlineG, ma->dyn, ma->rows);
   ma->n_inline = 1;
 }
 
@@ -1418,13 +1423,9 @@ sq_status sq_fork(sq_store *s, sq_seq parent, int64_t fork_len, sq_seq *child, v
 
   hipStream_t strm = static_cast<hipStream_t>(stream);
   s->last_stream = strm;
-  hipError_t e = sq::launch_copy_i32(s->pt_row(h), s->pt_row(parent), (int32_t)full, -1,
-                                     tail_page, strm);
-  if (e != hipSuccess) return hip_fail(e, "fork page-table copy");
-  if (tail) {
-    e = sq::launch_copy_page(s->pools, src_tail_page, tail_page, strm);
-    if (e != hipSuccess) return hip_fail(e, "fork tail copy");
-  }
+  hipError_t e = sq::launch_fork(s->pools, s->pt_row(h), s->pt_row(parent), (int32_t)full, src_tail_page,
+                                 tail_page, strm);
+  if (e != hipSuccess) return hip_fail(e, "fork");
   if (s->seqs[h].n_masked > 0) {
     sq_status r = upload_mask_row(s, h, strm);
     if (r != SQ_OK) return r;
@@ -1969,10 +1970,18 @@ sq_status sq_step_begin_ex(sq_store *s, const sq_seq *seqs, int32_t batch, int32
     s->step_pending[sb] = false;
   }
   sq::StepPlan *sp = s->device ? s->step_staging[sb] : nullptr;
+  const int32_t n_rows = batch * s->cfg.num_kv_heads <= sq::kStepRows ? batch * s->cfg.num_kv_heads : 0;
+  const size_t sp_bytes = window > 0 ? sizeof(sq::StepPlan)
+                                     : offsetof(sq::StepPlan, rows) + n_rows * sizeof(sq::MergeRows);
   if (sp) {
-    std::memset(sp, 0, sizeof(*sp));
+    std::memset(sp, 0, sp_bytes);
     fill_dyn(s, plan, sp->dec, &sp->merge);
-    if (window > 0) fill_dyn(s, plan_w, sp->dec_w, &sp->merge_w);
+    if (n_rows > 0) fill_rows(s, batch, s->cfg.num_kv_heads, sp->merge, sp->rows);
+    if (window > 0) {
+      fill_dyn(s, plan_w, sp->dec_w, &sp->merge_w);
+      if (n_rows > 0) fill_rows(s, batch, s->cfg.num_kv_heads, sp->merge_w, sp->rows_w);
+    }
+    sp->n_rows = n_rows;
   }
   const int64_t tok_bytes = (int64_t)s->cfg.num_kv_heads * s->cfg.head_dim * 2 * s->elem_bytes();
   TokenSlots t;
@@ -2017,10 +2026,8 @@ sq_status sq_step_begin_ex(sq_store *s, const sq_seq *seqs, int32_t batch, int32
       se.value[se.n] = t.page[b];
       ++se.n;
     }
-  hipError_t e = sq::launch_set_entries(se, strm);
-  if (e != hipSuccess) return hip_fail(e, "page-table entries");
-  e = hipMemcpyAsync(s->step_dev, sp, sizeof(*sp), hipMemcpyHostToDevice, strm);
-  if (e != hipSuccess) return hip_fail(e, "hipMemcpyAsync(step plan)");
+  hipError_t e = sq::launch_step_upload(s->step_dev, sp, (int64_t)sp_bytes, se, strm);
+  if (e != hipSuccess) return hip_fail(e, "step plan upload");
   e = hipEventRecord(s->step_ev[sb], strm);
   if (e != hipSuccess) return hip_fail(e, "hipEventRecord(step plan)");
   s->step_pending[sb] = true;

@@ -231,3 +231,26 @@ def test_step_arguments(sq):
         s.step_attn(0, kn, kn, q)
     torch.cuda.synchronize()
     s.close()
+
+
+@pytest.mark.parametrize("batch", [15, 16, 17, 24])
+@pytest.mark.parametrize("window", [0, 20])
+def test_step_batches_around_the_row_list_limit(sq, batch, window):
+    """Up to 128 (entry, KV head) pairs a step brings its merge row lists,
+    past that the merge derives them: with 8 KV heads the line lies between 16
+    and 17 entries, of lengths 0 and 1 up, forks among them."""
+    t = sc.Twin(sq, 2, 8, 8, 64, 500, 40, 40, seed=900 + batch)
+    seqs = []
+    for i in range(batch):
+        if i % 3 == 2:
+            h = t.fork(seqs[i - 1], t.model.info(seqs[i - 1])["length"])
+            t.append(h, 1 + i)
+        else:
+            h = t.create()
+            if i:
+                t.append(h, 1 + 23 * (i - 1))
+        seqs.append(h)
+    for _ in range(3):
+        err, _ = t.step(seqs, sq.ATTN_AUTO, window=window, layer_windows=[window, 0])
+        assert err <= TOL, err
+    t.check_state()
