@@ -292,7 +292,7 @@ sq_status sq_release(sq_store *store, sq_seq seq);
  * With SQ_STORE_EVICT_INPLACE the tail is written into the sequence's own
  * old pages instead (fresh pages only for pages another branch holds), one
  * launch per run of tail pages that read no page the run writes except
- * their own (each workgroup stages a page's sources before it writes it),
+ * their own (each workgroup loads a page's sources before it writes it),
  * or one pass in page order per (layer, KV head) where such runs are short.
  * With SQ_STORE_EVICT_REMAP a full tail page whose P kept tokens are one old
  * page's P tokens in order takes that old page by reference (no fresh page,

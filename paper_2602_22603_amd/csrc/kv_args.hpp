@@ -93,9 +93,9 @@ struct GatherArgs {
 // In-place eviction: tail pages [k0, k0 + n_pages) of the compacted
 // sequence, each filled from its kept tokens' old slots and written to
 // ids(k) (the old page at list index fp + k, or a fresh page).  Round mode
-// (sweep = 0): one workgroup per (page, layer * Hkv + head); no page of the
-// launch is read by another page of the launch.  Sweep mode (sweep = 1):
-// one workgroup per layer * Hkv + head takes the pages in order.
+// (sweep = 0): one workgroup per page and group of layer * Hkv + head rows; no
+// page of the launch is read by another page of the launch.  Sweep mode (sweep
+// = 1): one workgroup per group of rows takes the pages in order.
 struct InplaceArgs {
   int32_t fp;
   int32_t k0;
