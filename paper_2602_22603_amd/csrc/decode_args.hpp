@@ -163,7 +163,8 @@ struct StepAppend {
 // needs after one round of loads; without them it derives its own from the
 // tables, one dependent round after another (step of 22.7K tokens, 32/8 heads
 // of 128: 6.6 us a merge, 5.5 with the lists).  The upload is cut after
-// the last part the step uses.
+// the last part the step uses (a windowed plan that the step before left is
+// cleared).
 constexpr int kStepRows = 128;
 struct StepPlan {
   DecodeDyn dec[2];   // VALU, MFMA launch over every old token

@@ -351,6 +351,9 @@ struct sq_store {
   bool staging_pending = false;
   hipStream_t last_stream = nullptr;
   sq::StepPlan *step_dev = nullptr;     // the step plan in the workspace
+  // whether its windowed part may hold a plan (until the first upload:
+  // whatever the workspace held)
+  bool step_dev_windowed = true;
   // two pinned host copies of the plan, used in turn: a step waits only for
   // the upload of the step before the last, so the host runs a step ahead
   sq::StepPlan *step_staging[2] = {nullptr, nullptr};
@@ -1971,8 +1974,12 @@ sq_status sq_step_begin_ex(sq_store *s, const sq_seq *seqs, int32_t batch, int32
   }
   sq::StepPlan *sp = s->device ? s->step_staging[sb] : nullptr;
   const int32_t n_rows = batch * s->cfg.num_kv_heads <= sq::kStepRows ? batch * s->cfg.num_kv_heads : 0;
-  const size_t sp_bytes = window > 0 ? sizeof(sq::StepPlan)
-                                     : offsetof(sq::StepPlan, rows) + n_rows * sizeof(sq::MergeRows);
+  // A step without a window leaves out the windowed part, except after one
+  // with a window: that plan is cleared, so that a captured windowed layer
+  // replayed after this step attends to nothing of the other step's.
+  const bool with_windowed = window > 0 || s->step_dev_windowed;
+  const size_t sp_bytes = with_windowed ? sizeof(sq::StepPlan)
+                                        : offsetof(sq::StepPlan, rows) + n_rows * sizeof(sq::MergeRows);
   if (sp) {
     std::memset(sp, 0, sp_bytes);
     fill_dyn(s, plan, sp->dec, &sp->merge);
@@ -2028,6 +2035,7 @@ sq_status sq_step_begin_ex(sq_store *s, const sq_seq *seqs, int32_t batch, int32
     }
   hipError_t e = sq::launch_step_upload(s->step_dev, sp, (int64_t)sp_bytes, se, strm);
   if (e != hipSuccess) return hip_fail(e, "step plan upload");
+  s->step_dev_windowed = window > 0;
   e = hipEventRecord(s->step_ev[sb], strm);
   if (e != hipSuccess) return hip_fail(e, "hipEventRecord(step plan)");
   s->step_pending[sb] = true;

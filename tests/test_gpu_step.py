@@ -168,6 +168,48 @@ def test_captured_step_replays(sq, mi):
     t.check_state()
 
 
+@pytest.mark.parametrize("hkv,n_seqs", [(2, 2), (8, 17)])
+def test_windowed_replay_after_a_step_without_a_window(sq, hkv, n_seqs):
+    """A captured windowed layer replayed for a step that was begun without a
+    window finds no windowed plan, the one of a windowed step before it least
+    of all: it attends to the new token alone (whose weight is then 1).  With
+    and without merge row lists in the plan."""
+    import torch
+    hq, d, w = 2 * hkv, 64, 20
+    s = sq.Store(1, hq, hkv, d, 12 * n_seqs, n_seqs, 12, device="cuda")
+    seqs = []
+    for i in range(n_seqs):
+        a = s.seq_create()
+        k, v = (wl.device_normal_bf16((1, 40 + i, hkv, d), 2 * i + j, "cuda") for j in (0, 1))
+        s.append(a, k, v)
+        seqs.append(a)
+    kn, vn = (wl.device_normal_bf16((n_seqs, hkv, d), 900 + j, "cuda") for j in (0, 1))
+    q = wl.device_normal_bf16((n_seqs, hq, d), 950, "cuda")
+    out, ref = (torch.zeros((n_seqs, hq, d), dtype=torch.float32, device="cuda") for _ in range(2))
+    alone = vn.float().repeat_interleave(2, dim=1)     # [B][Hq][D]: the new token's V
+    s.step_begin(seqs, window=w)
+    s.step_attn(0, kn, vn, q, out=ref, window=w)       # eager: the step that the capture records
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        s.step_attn(0, kn, vn, q, out=out, window=w)
+    graph.replay()
+    torch.cuda.synchronize()
+    assert torch.equal(out, ref) and not torch.equal(out, alone)
+    for _ in range(3):
+        s.step_begin(seqs)
+        s.step_attn(0, kn, vn, q, out=ref)
+        out.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, alone)
+    s.step_begin(seqs, window=w)                       # and a windowed step's plan is found again
+    s.step_attn(0, kn, vn, q, out=ref, window=w)
+    graph.replay()
+    torch.cuda.synchronize()
+    assert torch.equal(out, ref) and not torch.equal(out, alone)
+    s.close()
+
+
 def _device_page_table(store, seq):
     """The device page-table mirror row of seq (the workspace starts with it:
     int32 [max_seqs][max_pages_per_seq])."""
