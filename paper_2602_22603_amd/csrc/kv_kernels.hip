@@ -383,8 +383,8 @@ __global__ __launch_bounds__(256) void k_write_ids(int32_t *dst, NewIds ids, int
 // The move of one destination page of one or more KV rows (row = layer * Hkv
 // + head; the rows of a pool are head_stride apart).
 //
-// Almost every page of a compacted tail is a run: its P kept tokens are P
-// consecutive old tokens, since spans and the runs between them are long.
+// Where spans and the stretches between them are long, almost every page of a
+// compacted tail is a run: its P kept tokens are P consecutive old tokens.
 // They lie in slots [slot0, P) of one old page and [0, slot0) of the next,
 // so the destination's K is P * D consecutive elements of the two, and a
 // 16-byte unit of its V^T is 16 bytes of two neighbouring units of a
@@ -449,9 +449,92 @@ __device__ inline void move_run(const Pools &p, int row0, int page_a, int page_b
   }
 }
 
-// Any other page (spans end or begin inside it, or it is the last and not
-// full): the same rows and units, each slot from its own old page, the
-// elements of a V^T unit one by one (they share their source's lines).
+// A page of a few runs (spans end or begin inside it, or it is the last and
+// not full): run r is the old tokens [src[r], ..) for slots [at[r], at[r + 1])
+// of the page (the last run ends at nv), its first token in old page page_a[r]
+// and its last in page_b[r].
+constexpr int kFewRuns = 4;
+struct FewRuns {
+  int n;
+  int at[kFewRuns], src[kFewRuns], last[kFewRuns], page_a[kFewRuns], page_b[kFewRuns];
+};
+
+// w with the bytes from n on (n <= 0: all, n >= 4: none) replaced by x's.
+__device__ inline uint32_t bytes_from(uint32_t w, uint32_t x, int n) {
+  const uint32_t m = n <= 0 ? ~0u : n >= 4 ? 0u : ~0u << (8 * n);
+  return (w & ~m) | (x & m);
+}
+
+// Such a page, moved as a page of one run is: a V^T unit is put together from
+// one funnel shift per run that reaches into it, the shift uniform for each
+// run, later runs over earlier ones, with every load in flight at once.
+// Of 16K tokens of 24 layers (8 heads of 128) 8 in every 10 kept: 579 us a
+// call, against 708 with each element from its own page, as pages of more
+// runs are moved, and 645 with the source pages staged in LDS; 8 in every 16:
+// 398, 465 and 424.  Not for an in-place eviction: its pages of one run got
+// slower by the registers (16K tokens of 24 layers of 64 channels, 400 of 700
+// kept: 463 -> 475 us with the appends).
+template <int D, class E>
+__device__ inline void move_few(const Pools &p, int row0, int nv, const FewRuns &f, int dst) {
+  constexpr int VU = kPageUnits<D, E>;
+  constexpr int U = VU / P;                // units per K row
+  constexpr int EPU = 16 / (int)sizeof(E); // V^T elements per unit
+  constexpr int UPC = P / EPU;             // units per channel's row
+  const int un = threadIdx.x % VU, row = row0 + threadIdx.x / VU;
+  const bool in = row < p.nl * p.hkv;
+  const int j = un / U, c = un % UPC;
+  auto unit = [&](uint16_t *pool, int page, int u) {
+    return reinterpret_cast<uint4 *>(reinterpret_cast<E *>(pool) + row * p.head_stride +
+                                     (int64_t)page * p.page_stride) + u;
+  };
+  uint4 k{}, v0[kFewRuns], v1[kFewRuns];
+  if (in) {
+    int src = f.src[0] + j, page = 0; // old token of K row j, and its page
+#pragma unroll
+    for (int r = 0; r < kFewRuns; ++r)
+      if (r < f.n && j >= f.at[r]) {
+        src = f.src[r] + j - f.at[r];
+        page = src / P == f.src[r] / P ? f.page_a[r] : f.page_b[r];
+      }
+    if (j < nv) k = *unit(p.k, page, src % P * U + un % U);
+  }
+#pragma unroll
+  for (int r = 0; r < kFewRuns; ++r) {
+    v0[r] = v1[r] = uint4{};
+    if (r >= f.n) continue;
+    const int len = f.last[r] - f.src[r] + 1;
+    // the old index that goes with the unit's first slot (no token moves
+    // up, so src >= at), its unit and the next, within those of the run
+    const int x = f.src[r] - f.at[r] + c * EPU, u0 = x / EPU;
+    const int lo = f.src[r] / EPU, hi = f.last[r] / EPU;
+    auto v_unit = [&](int u) {
+      return *unit(p.v, u / UPC == f.src[r] / P ? f.page_a[r] : f.page_b[r], un / UPC * UPC + u % UPC);
+    };
+    if (in && f.at[r] < (c + 1) * EPU && f.at[r] + len > c * EPU) {
+      if (u0 >= lo) v0[r] = v_unit(u0);
+      if (x % EPU != 0 && u0 < hi) v1[r] = v_unit(u0 + 1);
+    }
+  }
+  uint4 v{};
+#pragma unroll
+  for (int r = 0; r < kFewRuns; ++r) {
+    if (r >= f.n) continue;
+    const uint4 x = funnel16(v0[r], v1[r], (f.src[r] - f.at[r]) % EPU * (int)sizeof(E));
+    const int from = (f.at[r] - c * EPU) * (int)sizeof(E);
+    v = make_uint4(bytes_from(v.x, x.x, from), bytes_from(v.y, x.y, from - 4), bytes_from(v.z, x.z, from - 8),
+                   bytes_from(v.w, x.w, from - 12));
+  }
+  const int end = (nv - c * EPU) * (int)sizeof(E); // slots past the tokens: zero
+  v = make_uint4(bytes_from(v.x, 0u, end), bytes_from(v.y, 0u, end - 4), bytes_from(v.z, 0u, end - 8),
+                 bytes_from(v.w, 0u, end - 12));
+  if (in) {
+    if (j < nv) store_nt(unit(p.k, dst, un), k);
+    store_nt(unit(p.v, dst, un), v);
+  }
+}
+
+// Any other page: the same rows and units, each slot from its own old page,
+// the elements of a V^T unit one by one (they share their source's lines).
 // spage and sslot (LDS) hold the page id and slot of each of the nv sources.
 template <int D, class E, bool SYNC>
 __device__ inline void move_mixed(const Pools &p, int row0, int nv, const int *spage, const int *sslot,
@@ -504,15 +587,42 @@ __device__ inline void move_page(const Pools &p, int row0, int t0, int nv, int s
     if (with_pos) pos = p.pos[(int64_t)(s0 % P + t < P ? page_a : page_b) * P + (s0 + t) % P];
     move_run<D, E, SYNC>(p, row0, page_a, page_b, s0 % P, dst);
   } else {
-    if (t < nv) {
-      const int src = src_of(t0 + t);
-      spage[t] = pt_row[src / P];
-      sslot[t] = src % P;
+    FewRuns f;
+    f.n = kFewRuns + 1;
+    int src = 0;
+    if constexpr (SYNC) {
+      if (t < nv) src = src_of(t0 + t);
+    } else { // every wave finds the page's runs for itself, all of them the same
+      const int lane = t & 63;
+      if (lane < nv) src = src_of(t0 + lane);
+      const int before = __shfl_up(src, 1);
+      uint64_t starts = __ballot(lane < nv && (lane == 0 || src != before + 1));
+      f.n = __popcll(starts);
+#pragma unroll
+      for (int r = 0; r < kFewRuns; ++r) {
+        if (r >= f.n || f.n > kFewRuns) continue;
+        f.at[r] = __builtin_ctzll(starts);
+        starts &= starts - 1;
+        const int next = starts ? __builtin_ctzll(starts) : nv;
+        f.src[r] = __builtin_amdgcn_readlane(src, f.at[r]);
+        f.last[r] = f.src[r] + next - f.at[r] - 1;
+        f.page_a[r] = pt_row[f.src[r] / P];
+        f.page_b[r] = pt_row[f.last[r] / P];
+      }
     }
-    __syncthreads();
-    if (with_pos) pos = p.pos[(int64_t)spage[t] * P + sslot[t]];
-    move_mixed<D, E, SYNC>(p, row0, nv, spage, sslot, dst);
-    if constexpr (SYNC) __syncthreads(); // the next page reuses the LDS
+    if (f.n <= kFewRuns) {
+      if (with_pos) pos = p.pos[(int64_t)pt_row[src / P] * P + src % P];
+      move_few<D, E>(p, row0, nv, f, dst);
+    } else {
+      if (t < nv) {
+        spage[t] = pt_row[src / P];
+        sslot[t] = src % P;
+      }
+      __syncthreads();
+      if (with_pos) pos = p.pos[(int64_t)spage[t] * P + sslot[t]];
+      move_mixed<D, E, SYNC>(p, row0, nv, spage, sslot, dst);
+      if constexpr (SYNC) __syncthreads(); // the next page reuses the LDS
+    }
   }
   if (with_pos) p.pos[(int64_t)dst * P + t] = pos;
 }

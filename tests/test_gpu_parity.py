@@ -368,3 +368,49 @@ def test_evicted_pages_at_every_shift(sq, nl, hkv, d, kv8, kw):
             assert torch.equal(x, y), shift
         s.release(a)
     s.close()
+
+
+@pytest.mark.parametrize("kw", [{}, {"evict_inplace": True}, {"evict_chunk_pages": 3}, {"evict_remap": True}])
+@pytest.mark.parametrize("nl,hkv,d,kv8", [(1, 1, 128, False), (3, 1, 64, False), (1, 3, 128, True), (1, 5, 64, True)])
+def test_evicted_pages_of_few_and_many_runs(sq, nl, hkv, d, kv8, kw):
+    """Kept stretches and evicted spans of 1 to 33 tokens in random turn: pages
+    of one run up to sixteen, each run at any slot, within an old page or over
+    two, and last pages of 1 to 16 tokens of one or more runs: each kept token's
+    K, V and position bit for bit, and zeros in V after the last token."""
+    import torch
+    s = sq.Store(nl, hkv, hkv, d, 120, 2, 120, device="cuda", kv_scales=[[0.02, 0.03]] * nl if kv8 else None, **kw)
+    raw = torch.uint8 if kv8 else torch.int16
+
+    def held(h, n):
+        pt = torch.tensor(s.page_table(h), device="cuda")
+        tok = torch.arange(n, device="cuda")
+        pg, sl = pt[tok // 16], tok % 16
+        return (s.k_pool.view(raw)[:, :, pg, sl].clone(), s.v_pool.view(raw).transpose(3, 4)[:, :, pg, sl].clone(),
+                s.pos_pool[pg, sl].clone(), pt)
+
+    for seed in range(16):
+        rng = np.random.default_rng(77 + seed)
+        keep = []
+        while len(keep) < 700 + seed:
+            keep += [True] * int(rng.choice([1, 2, 3, 5, 8, 11, 15, 16, 17, 33]))
+            keep += [False] * int(rng.choice([1, 2, 3, 8, 15, 16, 17]))
+        keep = np.array(keep[:700 + seed])
+        a = s.seq_create()
+        k, v = (wl.to_torch_bf16(wl.normal_bf16(rng, (nl, len(keep), hkv, d)), "cuda") for _ in range(2))
+        s.append(a, k, v)
+        before = held(a, len(keep))
+        edges = np.flatnonzero(np.diff(np.concatenate(([1], keep.astype(int), [1]))))
+        spans = list(zip(edges[::2].tolist(), edges[1::2].tolist()))
+        for i, (x, y) in enumerate(spans):
+            s.span_mark(a, i, x, y)
+        s.evict(a, list(range(len(spans))))
+        at = torch.from_numpy(np.flatnonzero(keep)).to("cuda")
+        torch.cuda.synchronize()
+        after = held(a, len(at))
+        for i in (0, 1):
+            assert torch.equal(before[i][:, :, at], after[i]), (seed, i)
+        assert torch.equal(before[2][at], after[2]), seed
+        if len(at) % 16:
+            assert not s.v_pool.view(raw)[:, :, after[3][-1], :, len(at) % 16:].any(), seed
+        s.release(a)
+    s.close()
