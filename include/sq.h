@@ -201,6 +201,13 @@ typedef struct {
 } sq_plan_info;
 
 typedef struct {
+  int32_t rows;         /* query rows (tokens x query heads of a KV head) per workgroup */
+  int32_t n_qblocks;    /* query blocks of that many rows, per KV head */
+  int32_t n_split;      /* workgroups the key range of a query block is split over */
+  int32_t split_blocks; /* blocks of 64 keys per split */
+} sq_extend_info;
+
+typedef struct {
   /* Sums of kernel durations (ms) measured with HIP events recorded on the
      store's stream around each launch, over the calls made since profiling
      was enabled or last read.  evict_scan counts the eviction index kernel
@@ -491,6 +498,13 @@ sq_status sq_step_attn_ex(sq_store *store, int32_t layer, const void *k_new, con
 /* Host-only description of the work sq_decode_attn would do for this batch. */
 sq_status sq_decode_plan_info(sq_store *store, const sq_seq *seqs, int32_t batch,
                               int32_t mode, sq_plan_info *out);
+
+/* Host-only description of how sq_extend_attn_ex would cut the last n_new
+ * tokens of seq with this window (0: none) into workgroups.  A metadata-only
+ * store answers for a GPU of 256 compute units.  SQ_ERR_INVALID: n_new
+ * outside [1, length], window < 0, a head shape without a kernel. */
+sq_status sq_extend_plan_info(sq_store *store, sq_seq seq, int32_t n_new, int32_t window,
+                              sq_extend_info *out);
 
 /* ---- introspection -------------------------------------------------------*/
 sq_status sq_seq_info(sq_store *store, sq_seq seq, sq_seq_desc *out);

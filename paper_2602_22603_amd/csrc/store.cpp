@@ -838,6 +838,18 @@ struct ExtendPlan {
 // cost another one (77 tokens at 128 rows: 127 us with 504 workgroups, 177
 // with 528), and every split writes and reads partial rows (512 tokens: 577
 // us at one round, 602 at two rounds of half the keys).
+//
+// The prediction takes the splits of all query blocks for about equal, which
+// they are not in a chunk longer than its prefix: its early query blocks see
+// few keys, so of two splits the second is short or empty for half of them,
+// and with fewer than 8 KV heads the two fall on different XCDs.  Such a chunk
+// that would be cut in two runs 128 rows with an odd number of splits instead,
+// as many as four rounds of the CUs hold, at most five: 1.19x as fast in the
+// geometric mean of 126 such shapes, 0.98x at worst (8/1 heads of 128, 4140
+// tokens after 227: 114 us with two splits, 88 with three; 4/2 heads of 64,
+// 5484 after 40: 66 with two, 52 with five).  Two splits of 256 rows, one
+// round of the CUs, stay the better cut from a prefix of a third on (8/8 heads
+// of 64, 8-bit store, 4037 after 1833: 99 us, 115 with three of 128 rows).
 ExtendPlan plan_extend(const sq_store *s, int64_t n, int64_t L, int64_t window) {
   struct Tile {
     int rows, per_cu;
@@ -853,6 +865,13 @@ ExtendPlan plan_extend(const sq_store *s, int64_t n, int64_t L, int64_t window) 
   constexpr double kNarrow = 1.1;   // a narrow tile has to be this much better
   constexpr int64_t kMinBlocks = 2; // key blocks per split
   const int64_t hkv = s->cfg.num_kv_heads;
+  // the most splits of wg workgroups of `rows` rows over kb key blocks
+  // (k_extend_merge reads one split per lane, the partial rows have their
+  // place in the workspace)
+  auto most_splits = [&](int64_t rows, int64_t wg, int64_t kb) {
+    return std::max<int64_t>(
+        1, std::min<int64_t>({64, kb / kMinBlocks, (int64_t)sq::kMaxItems * sq::kRows / rows / wg}));
+  };
   ExtendPlan best{};
   double best_cost = 0;
   for (int t = 0; t < n_tiles; ++t) {
@@ -864,8 +883,7 @@ ExtendPlan plan_extend(const sq_store *s, int64_t n, int64_t L, int64_t window) 
     // a query block sees this many key blocks fewer than the one after it
     const double fewer = window > 0 ? 0.0 : (double)tq / sq::kExtKeys;
     const int64_t wg = qb * hkv, slots = (int64_t)s->cus * tiles[t].per_cu;
-    const int64_t most = std::max<int64_t>(
-        1, std::min<int64_t>({64, kb / kMinBlocks, (int64_t)sq::kMaxItems * sq::kRows / rows / wg}));
+    const int64_t most = most_splits(rows, wg, kb);
     for (int64_t r = 0; r <= 4; ++r) { // no split, then whole rounds of the CUs
       const int64_t split = r == 0 ? 1 : std::min(most, std::max<int64_t>(1, s->cus * r / wg));
       const int64_t all = wg * split, per = (kb + split - 1) / split;
@@ -893,6 +911,14 @@ ExtendPlan plan_extend(const sq_store *s, int64_t n, int64_t L, int64_t window) 
         best = {(int32_t)rows, (int32_t)qb, (int32_t)split, (int32_t)per};
       }
     }
+  }
+  const int64_t prefix = L - n;
+  if (best.n_split == 2 && window == 0 && n >= (best.rows == 256 ? 3 : 1) * prefix) {
+    const int64_t tq = 128 / s->G, qb = (n + tq - 1) / tq, kb = (L + sq::kExtKeys - 1) / sq::kExtKeys;
+    const int64_t four = 4 * (int64_t)s->cus / (qb * hkv);
+    const int64_t fit = std::max<int64_t>(1, std::min<int64_t>({5, four, most_splits(128, qb * hkv, kb)}));
+    const int64_t split = (fit - 1) / 2 * 2 + 1;
+    best = {128, (int32_t)qb, (int32_t)split, (int32_t)((kb + split - 1) / split)};
   }
   return best;
 }
@@ -2177,6 +2203,23 @@ sq_status sq_extend_attn_ex(sq_store *s, int32_t layer, sq_seq seq, int32_t n_ne
   const int64_t keys_read = o.window > 0 ? std::min<int64_t>(sqn->length, (int64_t)n_new + o.window - 1)
                                          : sqn->length;
   s->st.extend_kv_bytes += keys_read * (int64_t)s->cfg.num_kv_heads * s->D * 2 * s->elem_bytes();
+  return SQ_OK;
+}
+
+sq_status sq_extend_plan_info(sq_store *s, sq_seq h, int32_t n_new, int32_t window, sq_extend_info *out) {
+  if (!s || !out) return fail(SQ_ERR_INVALID, "null argument");
+  const Seq *q = s->get(h);
+  if (!q) return fail(SQ_ERR_UNKNOWN_SEQ, "unknown sequence %d", h);
+  if (n_new < 1 || n_new > q->length)
+    return fail(SQ_ERR_INVALID, "n_new %d outside [1, %lld]", n_new, (long long)q->length);
+  if (window < 0) return fail(SQ_ERR_INVALID, "window %d < 0", window);
+  if ((s->D != 64 && s->D != 128) || (s->G != 1 && s->G != 2 && s->G != 4 && s->G != 8))
+    return fail(SQ_ERR_INVALID, "no extend kernel for head_dim %d and %d query heads per KV head", s->D, s->G);
+  const ExtendPlan ep = plan_extend(s, n_new, q->length, window);
+  out->rows = ep.rows;
+  out->n_qblocks = ep.n_qblocks;
+  out->n_split = ep.n_split;
+  out->split_blocks = ep.split_blocks;
   return SQ_OK;
 }
 

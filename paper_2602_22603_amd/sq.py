@@ -78,6 +78,10 @@ class PlanInfo(C.Structure):
                 ("io_bytes", C.c_int64)]
 
 
+class ExtendInfo(C.Structure):
+    _fields_ = [(n, C.c_int32) for n in ("rows", "n_qblocks", "n_split", "split_blocks")]
+
+
 class AttnOpts(C.Structure):
     _fields_ = [("sinks", C.c_void_p), ("window", C.c_int32), ("reserved", C.c_int32)]
 
@@ -138,6 +142,8 @@ _SIGS = {
                                   C.c_void_p, C.c_float, C.POINTER(AttnOpts), C.c_void_p]),
     "sq_decode_plan_info": (C.c_int, [C.c_void_p, C.POINTER(C.c_int32), C.c_int32, C.c_int32,
                                       C.POINTER(PlanInfo)]),
+    "sq_extend_plan_info": (C.c_int, [C.c_void_p, C.c_int32, C.c_int32, C.c_int32,
+                                      C.POINTER(ExtendInfo)]),
     "sq_seq_info": (C.c_int, [C.c_void_p, C.c_int32, C.POINTER(SeqDesc)]),
     "sq_page_table": (C.c_int, [C.c_void_p, C.c_int32, C.POINTER(C.c_int32), C.c_int32,
                                 C.POINTER(C.c_int32)]),
@@ -492,6 +498,12 @@ class Store:
         _check(lib().sq_decode_plan_info(self._handle, _i32_array(seqs), len(seqs), mode,
                                          C.byref(pi)))
         return {n: getattr(pi, n) for n, _ in PlanInfo._fields_}
+
+    def extend_plan_info(self, seq, n, window=0):
+        """How extend() would cut the last n tokens of seq into workgroups."""
+        ei = ExtendInfo()
+        _check(lib().sq_extend_plan_info(self._handle, seq, n, window, C.byref(ei)))
+        return {n: getattr(ei, n) for n, _ in ExtendInfo._fields_}
 
     # -- introspection -------------------------------------------------------------
     def seq_info(self, seq):

@@ -683,3 +683,71 @@ def test_host_call_trace_from_environment(tmp_path):
     subprocess.run([sys.executable, "-c", code], check=True, env=env, timeout=120)
     calls = [re.match(r"sq (\w+)\(", l).group(1) for l in path.read_text().splitlines()]
     assert calls[:3] == ["sq_store_create", "sq_seq_create", "sq_append"]
+
+
+def _extend_plan(sq, hq, hkv, d, n, base, window=0):
+    s = sq.Store(num_layers=1, num_q_heads=hq, num_kv_heads=hkv, head_dim=d, num_pages=(n + base + 15) // 16,
+                 max_seqs=1, max_pages_per_seq=(n + base + 15) // 16, metadata_only=True)
+    a = s.seq_create()
+    s.append(a, n=n + base)
+    p = s.extend_plan_info(a, n, window=window)
+    s.close()
+    return p
+
+
+@pytest.mark.parametrize("hq,hkv,d", [(32, 8, 128), (64, 8, 64), (16, 8, 128), (8, 8, 64), (16, 2, 128), (8, 1, 128),
+                                      (4, 2, 64), (8, 8, 128)])
+def test_extend_plan_covers_every_key_and_fits_its_buffers(sq, hq, hkv, d):
+    """Over chunks of 1 to 40K tokens, prefixes and windows: the tile holds
+    whole tokens, the query blocks cover the chunk and the splits the keys of
+    the longest query block, and partial rows stay inside the workspace (8192
+    slots of 16 rows, up to 64 splits)."""
+    rng = np.random.default_rng(hq * 1000 + hkv)
+    for _ in range(250):
+        n = int(round(np.exp(rng.uniform(0, np.log(40000)))))
+        base = int(round(np.exp(rng.uniform(0, np.log(60000))))) - 1
+        w = int(rng.choice([0, 0, 1, 128, 5000]))
+        p = _extend_plan(sq, hq, hkv, d, n, base, w)
+        assert p["rows"] in ((256, 128, 64) if d == 128 else (256, 128))
+        tq = p["rows"] // (hq // hkv)
+        assert p["n_qblocks"] == -(-n // tq)
+        most = 0 # key blocks of the query block that sees the most
+        for qb in range(max(0, p["n_qblocks"] - 3), p["n_qblocks"]):
+            end = min(n + base, base + (qb + 1) * tq)
+            beg = max(0, base + qb * tq - w + 1) if w else 0
+            most = max(most, -(-end // 64) - beg // 64)
+        assert p["n_split"] * p["split_blocks"] >= most, (n, base, w, p)
+        assert 1 <= p["n_split"] <= 64
+        if p["n_split"] > 1:
+            assert p["n_qblocks"] * hkv * p["n_split"] * p["rows"] <= 8192 * 16
+
+
+@pytest.mark.parametrize("hq,hkv,d,n,base,rows,split", [
+    (8, 1, 128, 4140, 227, 128, 3), (8, 8, 64, 4161, 27, 128, 3), (4, 2, 64, 5484, 40, 128, 5),
+    (16, 8, 128, 882, 364, 128, 5), (8, 8, 128, 2944, 495, 128, 5), (16, 2, 128, 2805, 93, 128, 1),
+    (8, 8, 64, 4037, 1833, 256, 2), (16, 8, 128, 40, 39, 128, 1)])
+def test_extend_plan_of_a_chunk_longer_than_its_prefix(sq, hq, hkv, d, n, base, rows, split):
+    """Such a chunk is not cut in two (the second halves are short or empty for
+    half of the query blocks) but into an odd number of splits, up to five;
+    wide tiles may be, over a prefix of more than a third of the chunk."""
+    p = _extend_plan(sq, hq, hkv, d, n, base)
+    assert (p["rows"], p["n_split"]) == (rows, split)
+    for m in range(max(1, n // 2), 2 * n, max(1, n // 37)):
+        for b in (0, m // 9, m // 3, m // 2, m):
+            p = _extend_plan(sq, hq, hkv, d, m, b)
+            assert p["n_split"] != 2 or p["rows"] == 256 and m < 3 * b
+
+
+def test_extend_plan_arguments(sq):
+    s = _store(sq, 8, 16, 2, 8)          # head_dim 8: no kernel
+    a = s.seq_create()
+    s.append(a, n=20)
+    with pytest.raises(sq.SqError):
+        s.extend_plan_info(a, 4)
+    s = sq.Store(1, 8, 2, 64, 8, 2, 8, metadata_only=True)
+    a = s.seq_create()
+    s.append(a, n=20)
+    for seq, n, w in ((a, 0, 0), (a, 21, 0), (a, 4, -1), (1, 4, 0)):
+        with pytest.raises(sq.SqError):
+            s.extend_plan_info(seq, n, window=w)
+    assert s.extend_plan_info(a, 20)["n_split"] == 1
