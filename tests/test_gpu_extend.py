@@ -111,10 +111,11 @@ def test_extend_several_query_blocks(sq, hq, hkv, d, prefix, n):
 @pytest.mark.parametrize("hq,hkv,d", [(8, 2, 128), (4, 1, 64)])
 @pytest.mark.parametrize("length", [64, 128, 192, 200, 256, 300, 384, 420])
 def test_extend_key_block_counts(sq, hq, hkv, d, length):
-    """One query block (a 16-token chunk) against 1 to 7 blocks of 64 keys,
-    full and ragged: the kernel cycles its three block buffers a whole turn
-    at a time and takes the last one or two blocks after the loop, so every
-    count of turns and of blocks left over is covered."""
+    """One query block (a 16-token chunk, which runs a 128-row tile) against 1
+    to 7 blocks of 64 keys, full and ragged: the kernel cycles its block
+    buffers (three at 64 channels, two at 128) a whole turn at a time and
+    takes what is left after the loop, so every count of turns and of blocks
+    left over is covered."""
     n = 16
     tw = _twin(sq, hq, hkv, d, length, seed=170 + length)
     a = tw.create()
@@ -130,14 +131,16 @@ def test_extend_key_block_counts(sq, hq, hkv, d, length):
 @pytest.mark.parametrize("prefix", [0, 70, 190])
 def test_extend_row_tile_edges(sq, hq, hkv, d, rows, prefix):
     """Chunks whose query rows (tokens x heads per KV head) just fill, or just
-    pass, the 64- and 128-row tiles that short chunks run on, against odd and
-    even counts of key blocks (those tiles alternate two block buffers)."""
+    pass, half a 128-row tile, a whole one and two, the tile they all run on
+    after a short prefix, against odd and even counts of key blocks (at 128
+    channels that tile alternates two block buffers)."""
     n = -(-rows // (hq // hkv))
     tw = _twin(sq, hq, hkv, d, prefix + n, seed=190 + rows + prefix)
     a = tw.create()
     if prefix:
         tw.append(a, prefix)
     tw.append(a, n)
+    assert tw.store.extend_plan_info(a, n)["rows"] == 128
     err = _extend_error(tw, a, n)
     print(f"extend hq={hq} hkv={hkv} d={d} prefix={prefix} n={n}: max abs err {err:.2e}")
     assert err <= TOL
@@ -153,6 +156,8 @@ def test_extend_wide_tile_key_block_counts(sq, d):
     tw = _twin(sq, 32, 8, d, n, seed=211)
     a = tw.create()
     tw.append(a, n)
+    plan = tw.store.extend_plan_info(a, n)
+    assert (plan["rows"], plan["n_split"]) == (256, 1)
     blocks = list(range(9)) + [61, 62, 63]
     err = _extend_error(tw, a, n, pairs=[(64 * b + j, (b + j) % 8) for b in blocks for j in (0, 63)])
     print(f"extend d={d} n={n}: max abs err {err:.2e}")

@@ -206,7 +206,7 @@ def test_fp8_extend(sq, hq, hkv, d, prefix, n, window):
 @pytest.mark.parametrize("length", [128, 192, 256, 300])
 def test_fp8_extend_key_block_counts(sq, length):
     """An 8-bit store's extend over 2 to 5 blocks of 64 keys (its converted
-    copies rotate through the kernel's block buffers like the bf16 ones)."""
+    copies alternate two block buffers)."""
     import math
     import torch
     from oracle import extend as oex
