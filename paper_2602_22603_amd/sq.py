@@ -202,11 +202,15 @@ def _ptr(t):
 def _stream(stream):
     if stream is None:
         # the current stream's handle without a Stream object around it: 0.4
-        # against 3.0 us, a fifth of a small decode call's host time
+        # against 3.0 us, a fifth of a small decode call's host time (not part
+        # of torch's documented interface, so not taken for granted)
         import torch
-        if not torch.cuda.is_initialized():
-            torch.cuda.init()
-        return C.c_void_p(torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice()))
+        try:
+            if torch.cuda.is_initialized():
+                return C.c_void_p(torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice()))
+        except AttributeError:
+            pass
+        return C.c_void_p(torch.cuda.current_stream().cuda_stream)
     if isinstance(stream, int):
         return C.c_void_p(stream)
     return C.c_void_p(stream.cuda_stream)

@@ -751,3 +751,23 @@ def test_extend_plan_arguments(sq):
         with pytest.raises(sq.SqError):
             s.extend_plan_info(seq, n, window=w)
     assert s.extend_plan_info(a, 20)["n_split"] == 1
+
+
+def test_current_stream_with_and_without_the_raw_handle(sq, monkeypatch):
+    """No stream given: the current device's raw handle, or the Stream
+    object's where torch has no such call."""
+    import torch
+
+    class Current:
+        cuda_stream = 4321
+
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: Current)
+    monkeypatch.setattr(torch.cuda, "is_initialized", lambda: True)
+    monkeypatch.setattr(torch._C, "_cuda_getDevice", lambda: 3, raising=False)
+    monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda device: 1000 + device, raising=False)
+    assert sq._stream(None).value == 1003
+    monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream")
+    assert sq._stream(None).value == 4321
+    monkeypatch.setattr(torch.cuda, "is_initialized", lambda: False)
+    assert sq._stream(None).value == 4321
+    assert sq._stream(17).value == 17 and sq._stream(Current).value == 4321
