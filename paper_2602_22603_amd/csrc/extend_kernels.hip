@@ -52,8 +52,8 @@ namespace {
 
 constexpr int BK = kExtKeys;
 constexpr float kNegInf = -__builtin_huge_valf();
-// Two waves per SIMD: the eight waves of the one workgroup a CU holds (up
-// to 256 registers each).
+// Two waves per SIMD (up to 256 registers each): the eight waves of the one
+// 256-row workgroup a CU holds, or of two with 128 rows.
 constexpr int kExtWavesPerEu = 2;
 
 typedef __bf16 bf16x2_t __attribute__((__vector_size__(2 * sizeof(__bf16))));
@@ -114,8 +114,9 @@ template <int D, int W> struct ExtLayout {
   static constexpr int KPP = kPage / KROWS; // K copy instructions that fill a page
   static constexpr int VPP = kPage * D * 2 / 1024; // and V^T ones
   static constexpr int NP = NK > KPP ? NK / KPP : 1; // pages a wave's copies cover
-  // block buffers: two for an 8-bit store (whose copies pass through
-  // registers) and where two or more workgroups are to share a CU's LDS
+  // block buffers of a bf16 store: three, or two where two workgroups are to
+  // share a CU's LDS (an 8-bit store, whose next block passes through
+  // registers, uses two whatever the tile; the third then takes no LDS)
   static constexpr int NB = D == 128 && W < 8 ? 2 : 3;
   static_assert(KPP == VPP && (NK % KPP == 0 || KPP % NK == 0), "a wave copies whole pages or a part of one");
 };
@@ -500,9 +501,9 @@ k_extend(ExtendArgs a) {
   const uint8_t *vbase8 = reinterpret_cast<const uint8_t *>(a.v) + (int64_t)g * a.head_stride;
   uint2 kr[Lt::NK], vr[Lt::NV]; // an 8-bit store's next block, in flight
   int32_t ids[4];
-  // Copies run two blocks ahead (one for an 8-bit store, whose next block
+  // Copies run NB - 1 blocks ahead (one for an 8-bit store, whose next block
   // passes through registers): ids holds the page ids of the next block to
-  // be fetched.  The copies of the two blocks past b_hi are issued too (of
+  // be fetched.  The copies of the NB - 1 blocks past b_hi are issued too (of
   // the last page, block_ids clamps) into buffers that no block reads: with
   // a copy issued at the top of every block, the copies in flight at each
   // block's top are the same on every path, which the compiler can follow,
@@ -524,7 +525,7 @@ k_extend(ExtendArgs a) {
     }
     block_ids(ids, a, KV8 || NB == 2 ? b_lo + 1 : b_lo + 2);
     // block b from buffers c; buffers n1 and n2 are those of blocks b + 1 and
-    // b + 2 (an 8-bit store uses only two buffers)
+    // b + 2 (with two buffers, and for an 8-bit store, n2 is c)
     auto block = [&](int b, uint16_t *ck, uint16_t *cv, uint16_t *n1k, uint16_t *n1v,
                      uint16_t *n2k, uint16_t *n2v) __attribute__((always_inline)) {
       // keep bits of this lane's 16 keys of the block (deferred evictions)
@@ -546,9 +547,9 @@ k_extend(ExtendArgs a) {
           lm = ((lo >> sh) & 0xffu) | (((hi >> sh) & 0xffu) << 8);
         }
       }
-      // block b has landed (every wave's copies; those of block b + 1, issued
-      // later, may still be in flight) and every wave is done with block
-      // b - 1, whose buffer the next copy overwrites
+      // block b has landed (every wave's copies; with three buffers those of
+      // block b + 1, issued later, may still be in flight) and every wave is
+      // done with block b - 1, whose buffer the next copy overwrites
       __builtin_amdgcn_s_waitcnt(KV8 ? 0 : kVmcntKeep<NB == 2 ? 0 : Lt::NK + Lt::NV>);
       lds_barrier();
       if ((b + 1) * BK > a.L) {

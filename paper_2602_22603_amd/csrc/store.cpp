@@ -1795,19 +1795,19 @@ sq_status sq_evict_spans_ex(sq_store *s, sq_seq h, const int32_t *cursor_ids, in
     // layer).  Searching the spans lengthens each gather workgroup, though, a
     // cost that grows with the launch: 30K tokens of 4 layers (36K pages and
     // rows) took 105 us so against 97, 60K of an 8-bit store 112 against 97.
-    // So a launch of more than kFuseIndexMaxWgs (page, row) pairs keeps the
+    // So a launch of more than kFuseIndexMaxPairs (page, row) pairs keeps the
     // index kernel, as do the in-place kernel, an eviction that copies no
     // page, and spans too many to travel in the arguments; the gathers then
     // read src_of.
-    constexpr int64_t kFuseIndexMaxWgs = 12288;
-    int64_t first_wgs = 0;
+    constexpr int64_t kFuseIndexMaxPairs = 12288;
+    int64_t first_pairs = 0;
     if (!inplace)
       for (const Step &st : steps)
         if (st.c != 0 && fresh_in(st.k0, st.c) != 0) {
-          first_wgs = st.c * (int64_t)s->cfg.num_layers * s->cfg.num_kv_heads;
+          first_pairs = st.c * (int64_t)s->cfg.num_layers * s->cfg.num_kv_heads;
           break;
         }
-    const bool fuse_index = first_wgs > 0 && first_wgs <= kFuseIndexMaxWgs && spans_inline;
+    const bool fuse_index = first_pairs > 0 && first_pairs <= kFuseIndexMaxPairs && spans_inline;
     ProfPair pp;
     bool on = false;
     hipError_t e = hipSuccess;
