@@ -51,6 +51,10 @@ __device__ inline void store_nt(void *dst, uint4 x) {
 __device__ inline void store_nt(void *dst, uint2 x) {
   __builtin_nontemporal_store(nt2_t{x.x, x.y}, static_cast<nt2_t *>(dst));
 }
+template <bool NT, class T> __device__ inline void store_as(void *dst, T x) {
+  if constexpr (NT) store_nt(dst, x);
+  else *static_cast<T *>(dst) = x;
+}
 
 // ---------------------------------------------------------------------------
 // Append.  New tokens come token-major [NL][n_total][Hkv][D]; K rows are
@@ -63,13 +67,15 @@ __device__ inline void store_nt(void *dst, uint2 x) {
 // The kernel is bound by HBM: each byte is read once and written once.  A
 // workgroup takes one 8 KB unit of work (a page of 128 channels, two of 64)
 // with every load in flight before the first store; groups of twice that were
-// 1-4% slower.  Pages are stored non-temporally, so that they do not push the
-// source out of the caches on their way: 8192 tokens of 24 layers (8 heads of
-// 128) 322 -> 294 us, 8000 tokens of 2 heads 89 -> 65 us.  The source is
-// loaded non-temporally too (NTL) when it is larger than the 256 MB memory-side
-// cache, so that little of it can be there: 294 -> 280 us (5.8 TB/s); a smaller
-// one may still be there from the projection that wrote it (3000 tokens of 12
-// layers, 147 MB, just read: 48 us, with non-temporal loads 51).
+// 1-4% slower.  NT says what passes the caches by, against the 256 MB
+// memory-side cache.  0, source and pages fit it together: nothing, since the
+// decode that follows reads the pages, and the projection before wrote the
+// source (512 tokens of 24 layers of 8 heads of 128, then a decode of each layer:
+// 253 us of GPU time, 267 with NT 1).  1, they do not: the pages, which would
+// push the source out (8192 tokens of 24 layers 322 -> 294 us; 2048, with the
+// decodes, 332 -> 319).  2, the source alone is larger: its loads too (294 ->
+// 280 us, 5.8 TB/s; 3000 tokens of 12 layers, 147 MB, just read: 48 us, 51 with
+// NT 2).
 __device__ inline float bf16_val(uint16_t b) { return __uint_as_float((uint32_t)b << 16); }
 __device__ inline uint2 quant8(uint4 w, float inv) { // 8 bf16 -> 8 codes
   const uint32_t x[4] = {w.x, w.y, w.z, w.w};
@@ -82,7 +88,7 @@ __device__ inline uint2 quant8(uint4 w, float inv) { // 8 bf16 -> 8 codes
 
 template <int D> constexpr int kAppendGroup = 128 / D; // pages of one workgroup
 
-template <int D, class E, bool NTL>
+template <int D, class E, int NT>
 __global__ __launch_bounds__(256) void k_append(Pools p, AppendArgs a,
                                                 const uint16_t *__restrict__ kn,
                                                 const uint16_t *__restrict__ vn) {
@@ -116,8 +122,8 @@ __global__ __launch_bounds__(256) void k_append(Pools p, AppendArgs a,
       const int idx = r * 256 + threadIdx.x;
       if (N * PT < 256 && idx >= N * PT) break;
       const int64_t src = (t0 + idx / U) * tok_stride + idx % U * 8;
-      kr[r] = load16<NTL>(ks + src);
-      vr[r] = load16<NTL>(vs + src);
+      kr[r] = load16<NT == 2>(ks + src);
+      vr[r] = load16<NT == 2>(vs + src);
     }
 #pragma unroll
     for (int r = 0; r < NR; ++r) {
@@ -130,8 +136,8 @@ __global__ __launch_bounds__(256) void k_append(Pools p, AppendArgs a,
       const int idx = r * 256 + threadIdx.x;
       if (N * PT < 256 && idx >= N * PT) break;
       E *kd = kpage(i0 + idx / PT) + idx % PT * 8;
-      if constexpr (KV8) store_nt(kd, quant8(kr[r], inv_k));
-      else store_nt(kd, kr[r]);
+      if constexpr (KV8) store_as<NT != 0>(kd, quant8(kr[r], inv_k));
+      else store_as<NT != 0>(kd, kr[r]);
     }
     __syncthreads();
 #pragma unroll
@@ -145,8 +151,8 @@ __global__ __launch_bounds__(256) void k_append(Pools p, AppendArgs a,
         w[e] = (uint32_t)tile[i][h * 8 + 2 * e][d] | (uint32_t)tile[i][h * 8 + 2 * e + 1][d] << 16;
       const uint4 o = make_uint4(w[0], w[1], w[2], w[3]);
       E *vd = vpage(i0 + i) + d * P + h * 8;
-      if constexpr (KV8) store_nt(vd, quant8(o, inv_v));
-      else store_nt(vd, o);
+      if constexpr (KV8) store_as<NT != 0>(vd, quant8(o, inv_v));
+      else store_as<NT != 0>(vd, o);
     }
   };
   if (tok >= 0 && tok + NPG * P <= a.n_tok) {
@@ -729,11 +735,13 @@ template <int D, class E>
 hipError_t append_dispatch(const Pools &p, const AppendArgs &a, const uint16_t *kn,
                            const uint16_t *vn, hipStream_t s) {
   const dim3 grid((a.n_pages + kAppendGroup<D> - 1) / kAppendGroup<D>, p.nl * p.hkv), block(256);
-  const bool beyond = (int64_t)p.nl * a.n_total * p.hkv * D * 4 > kMemSideCache; // K and V
-  if (beyond)
-    hipLaunchKernelGGL((k_append<D, E, true>), grid, block, 0, s, p, a, kn, vn);
+  const int64_t elems = 2ll * p.nl * a.n_total * p.hkv * D; // K and V
+  if (elems * 2 > kMemSideCache)
+    hipLaunchKernelGGL((k_append<D, E, 2>), grid, block, 0, s, p, a, kn, vn);
+  else if (elems * (int64_t)(2 + sizeof(E)) > kMemSideCache)
+    hipLaunchKernelGGL((k_append<D, E, 1>), grid, block, 0, s, p, a, kn, vn);
   else
-    hipLaunchKernelGGL((k_append<D, E, false>), grid, block, 0, s, p, a, kn, vn);
+    hipLaunchKernelGGL((k_append<D, E, 0>), grid, block, 0, s, p, a, kn, vn);
   return hipGetLastError();
 }
 } // namespace

@@ -258,9 +258,10 @@ def test_merge_row_lists_in_arguments_and_from_the_plan(sq, hq, hkv):
 
 @pytest.mark.parametrize("d,kv8", [(128, False), (64, False), (128, True)])
 def test_append_larger_than_the_memory_side_cache(sq, d, kv8):
-    """An append whose source exceeds 256 MB (non-temporal loads) stores what
-    the same tokens stored in halves do (ordinary loads), bit for bit, on both
-    sides of the line and from a ragged slot on."""
+    """An append whose source exceeds 256 MB (non-temporal loads and stores), or
+    does so with its pages (non-temporal stores), stores what the same tokens
+    stored in halves do (neither), bit for bit, on both sides of the first line
+    and from a ragged slot on."""
     import torch
     nl, hkv, base = 8, 8, 5
     for n in ((256 << 20) // (nl * hkv * d * 4), (256 << 20) // (nl * hkv * d * 4) + 1):
